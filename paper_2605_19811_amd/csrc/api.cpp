@@ -105,6 +105,8 @@ StagingRing g_ring;
 // binding table (one TensorPtrs per input tensor), rewritten on the call's
 // stream whenever a call brings other tensor addresses than the previous
 // call of the plan.
+constexpr int kTaskLists = 7;
+
 struct DevicePlan {
   Plan plan;
   int device = -1;
@@ -122,8 +124,9 @@ struct DevicePlan {
   lm::SrBlock* d_sr_tab = nullptr;
   int32_t* d_rd_start = nullptr;
   int32_t* d_tensor_mat = nullptr;
-  lm::GemmTask* d_tasks[2][4] = {};   // [precision][gram, poly, apply, apply tail]
-  lm::XcdSplit* d_splits = nullptr;   // [precision * 4 + list]
+  // [precision][gram, poly, apply, apply tail, fine gram, fine poly, fine apply]
+  lm::GemmTask* d_tasks[2][kTaskLists] = {};
+  lm::XcdSplit* d_splits = nullptr;   // [precision * kTaskLists + list]
 
   ~DevicePlan() {
     if (last_use) (void)hipEventDestroy(last_use);
@@ -281,7 +284,7 @@ struct TableImage {
   std::vector<uint8_t> bytes;
   size_t o_bind = 0, o_lion = 0, o_lion_start = 0, o_mats = 0, o_prep = 0, o_sr = 0, o_rd = 0,
          o_tm = 0, o_splits = 0;
-  size_t o_tasks[2][4] = {};
+  size_t o_tasks[2][kTaskLists] = {};
 };
 
 void pack_tables(Plan& p, std::vector<lm::TensorPtrs>& bind, TableImage* img) {
@@ -305,6 +308,10 @@ void pack_tables(Plan& p, std::vector<lm::TensorPtrs>& bind, TableImage* img) {
     splits.push_back(p.poly_split[pr]);
     splits.push_back(p.apply_split[pr]);
     splits.push_back(p.apply_tail_split[pr]);
+    for (int st = 0; st < 3; ++st) {
+      img->o_tasks[pr][4 + st] = off; place(p.fine[pr][st], &off, &parts);
+      splits.push_back(p.fine_split[pr][st]);
+    }
   }
   img->o_splits = off;     place(splits, &off, &parts);
   img->bytes.assign(std::max<size_t>(off, 256), 0);
@@ -324,8 +331,8 @@ void point_tables(DevicePlan* dp, uint8_t* base, const TableImage& img) {
   dp->d_rd_start = reinterpret_cast<int32_t*>(base + img.o_rd);
   dp->d_tensor_mat = reinterpret_cast<int32_t*>(base + img.o_tm);
   for (int pr = 0; pr < 2; ++pr)
-    for (int st4 = 0; st4 < 4; ++st4)
-      dp->d_tasks[pr][st4] = reinterpret_cast<lm::GemmTask*>(base + img.o_tasks[pr][st4]);
+    for (int k = 0; k < kTaskLists; ++k)
+      dp->d_tasks[pr][k] = reinterpret_cast<lm::GemmTask*>(base + img.o_tasks[pr][k]);
   dp->d_splits = reinterpret_cast<lm::XcdSplit*>(base + img.o_splits);
 }
 
@@ -609,18 +616,24 @@ lm_status enqueue(const DevicePlan& dp, const lm::StepConsts& k, const lm_config
     for (int st3 = 0; st3 < 3; ++st3) {
       Timer t(stream, phases[st3]);
       for (int pr = 0; pr < 2; ++pr) {   // bf16 matrices, then fp32 matrices
-        const lm::XcdSplit& sp = st3 == 0 ? p.gram_split[pr] : (st3 == 1 ? p.poly_split[pr]
-                                                                          : p.apply_split[pr]);
+        const lm::GemmVariant& v = p.variant[pr][st3];
+        const bool fine = v.tile > 0;
+        const lm::XcdSplit& sp = fine ? p.fine_split[pr][st3]
+                                      : (st3 == 0 ? p.gram_split[pr]
+                                                  : (st3 == 1 ? p.poly_split[pr] : p.apply_split[pr]));
         if (sp.max_count == 0) continue;
-        gl.tasks = dp.d_tasks[pr][st3];
-        gl.split = dp.d_splits + pr * 4 + st3;
+        const int list = fine ? 4 + st3 : st3;
+        gl.tasks = dp.d_tasks[pr][list];
+        gl.split = dp.d_splits + pr * kTaskLists + list;
         gl.max_count = sp.max_count;
         gl.fp32 = pr;
-        gl.tile = p.tile[pr][st3];
+        gl.tile = fine ? v.tile : p.tile[pr][st3];
+        gl.bufs = v.bufs;
+        gl.groups = v.groups;
         // the apply's last round as smaller tiles, in the same launch
-        const bool tail = st3 == 2 && p.apply_tail_split[pr].max_count > 0;
+        const bool tail = !fine && st3 == 2 && p.apply_tail_split[pr].max_count > 0;
         gl.tail_tasks = tail ? dp.d_tasks[pr][3] : nullptr;
-        gl.tail_split = tail ? dp.d_splits + pr * 4 + 3 : nullptr;
+        gl.tail_split = tail ? dp.d_splits + pr * kTaskLists + 3 : nullptr;
         gl.tail_max_count = tail ? p.apply_tail_split[pr].max_count : 0;
         gl.tail_tile = tail ? p.tail_tile[pr] : 0;
         e = lm::launch_gemm(modes[st3], gl, stream);
@@ -818,6 +831,10 @@ lm_status step_noalloc_impl(float* const* params, const float* const* grads,
     if (st != Status::kOk) return fail(to_c(st), err);
     TableImage img;
     pack_tables(p, bind, &img);
+    if (align256(img.bytes.size()) + p.ws_bytes > lm::kScratchBytes) {
+      lm::drop_fine(&p);                   // the usual tiles need no tables of their own
+      pack_tables(p, bind, &img);
+    }
     const size_t ws_off = align256(img.bytes.size());
     const size_t need = ws_off + p.ws_bytes;
     if (need > lm::kScratchBytes)

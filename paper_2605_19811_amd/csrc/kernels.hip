@@ -922,9 +922,14 @@ __global__ __launch_bounds__(256) void srank_decide_kernel(SrankArgs a) {
 //             blocks (32 B of operand loads per CU-clock at full MFMA rate);
 //   BT = 128: 4 waves (2 x 2), each a 64 x 64 sub-tile of 2 x 2 blocks, for
 //             stages with too few 256-tiles to fill the chip;
-//   BT = 64:  4 waves (2 x 2), each one 32 x 32 block (fp32 products with
-//             too few 128-tiles to fill the chip, and the bf16 apply's last
+//   BT = 64:  4 waves (2 x 2), each one 32 x 32 block (products with too few
+//             larger tiles to fill the chip, and the bf16 apply's last
 //             round when sixteen times its leftover 256-tiles fit one round).
+// A small tile alone on its CU is bound by latency: 0.27 us a K stage of a
+// 64-tile with four LDS stages, 0.46 with two, 0.78 of a 128-tile with two.
+// So short lists take four stages, or (one tile per CU at most) four stages
+// in each of KG = 2 groups of waves that share the K loop (0.20 us a stage);
+// longer ones two stages, and four workgroups to a CU.
 // Accumulator element r of block (mi, ni) sits at row
 // wm + 32 mi + 8 (r / 4) + 4 (lane / 32) + r % 4, col wn + 32 ni + lane % 32.
 // Wait until at most N vector-memory operations of this wave are outstanding
@@ -937,6 +942,18 @@ __device__ __forceinline__ void wait_vmcnt() {
   // s_waitcnt fields: vmcnt[3:0] in bits 3:0, vmcnt[5:4] in 15:14; expcnt
   // (6:4) and lgkmcnt (11:8) at their maxima, i.e. not waited for
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// Wait until at most n stages of OPS copies, and EXTRA operations besides,
+// are outstanding (n wave-uniform, 0 <= n <= N).
+template <int N, int OPS, int EXTRA>
+__device__ __forceinline__ void wait_stages(int n) {
+  if constexpr (N > 0) {
+    if (n >= N) wait_vmcnt<EXTRA + N * OPS>();
+    else wait_stages<N - 1, OPS, EXTRA>(n);
+  } else {
+    wait_vmcnt<EXTRA>();
+  }
 }
 
 // Descriptor tables are read through the constant address space: they are
@@ -1048,7 +1065,7 @@ struct GemmArgs {
 
 // LDS of one product tile: kNBuf operand stages during the K loop, then the
 // output tile (the kernel declares it; the tile body takes a pointer).
-template <typename T, int MODE, int BT>
+template <typename T, int MODE, int BT, int NB = 0, int KG = 1>
 struct GemmLds {
   static constexpr int kLd = Mfma<T>::kBK;      // LDS row: 128 bytes
   static constexpr int kStR = BT + 16;          // row-major staging row stride
@@ -1056,8 +1073,9 @@ struct GemmLds {
   // empty last round of 256-tiles, one or two such workgroups per CU and too
   // few of them to hide load latency with other workgroups): four, three of
   // them in flight while one feeds the MFMAs.
-  static constexpr int kNBuf = (MODE == kApply && BT <= 128 && sizeof(T) == 2) ? 4 : 2;
-  static constexpr int kOperand = kNBuf * 2 * BT * kLd, kStage = BT * kStR;
+  // NB > 0 sets the count (64-tiles of lists that leave CUs idle).
+  static constexpr int kNBuf = NB > 0 ? NB : (sizeof(T) == 2 && (BT == 64 || (MODE == kApply && BT == 128))) ? 4 : 2;
+  static constexpr int kOperand = kNBuf * KG * 2 * BT * kLd, kStage = BT * kStR;
   static constexpr int kElems = kOperand > kStage ? kOperand : kStage;
   static constexpr int kBytes = kElems * int(sizeof(T));
 };
@@ -1067,7 +1085,7 @@ struct GemmLds {
 // on every other apply step). `smem` is the kernel's LDS block (at least
 // GemmLds<T, MODE, BT>::kBytes); the workgroup is number `bid` of the `nblk`
 // that run this task list (workgroup i on XCD i mod xcds).
-template <typename T, int MODE, int BT, bool LAST = false>
+template <typename T, int MODE, int BT, bool LAST = false, int NB = 0, int KG = 1>
 __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, int nblk) {
   using M = Mfma<T>;
   using Geo = TileGeom<BT>;
@@ -1080,15 +1098,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // rows, 8 or 16 dwords apart modulo the 64 banks, so a quad of lanes
   // writing 4 consecutive rows never collides), kStC for transposed staging
   // (4 dwords apart, so 16 lanes writing 16 consecutive rows never collide).
-  using L = GemmLds<T, MODE, BT>;
+  using L = GemmLds<T, MODE, BT, NB, KG>;
   constexpr int kStR = L::kStR, kStC = BT + kEpc;
   constexpr int kNBuf = L::kNBuf;
-  T (*sA)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem);
-  T (*sB)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem + kNBuf * BT * kLd);
+  // K groups: the waves of group kg take every KG-th K stage, into buffers of
+  // their own; their sums meet in LDS after the K loop.
+  const int kg = KG == 1 ? 0 : int(__builtin_amdgcn_readfirstlane(threadIdx.x / kNT));
+  T* smem_g = smem + kg * (kNBuf * 2 * BT * kLd);
+  T (*sA)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g);
+  T (*sB)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g + kNBuf * BT * kLd);
   // apply: the B operand (X, K = s along its rows) is staged k-major as
   // kBK rows of BT elements (512 bytes) and read transposed
   constexpr bool kBRows = MODE == kApply;
-  T (*sBr)[kBK][BT] = reinterpret_cast<T (*)[kBK][BT]>(smem + kNBuf * BT * kLd);
+  T (*sBr)[kBK][BT] = reinterpret_cast<T (*)[kBK][BT]>(smem_g + kNBuf * BT * kLd);
 
   // The workgroups of an XCD walk that XCD's tile list with a stride of
   // their number, skipping the tiles of matrices whose adaptive decision
@@ -1097,7 +1119,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // registers, so the next tile's loads overlap them. The other products
   // stage their results through the whole LDS and run one tile per
   // workgroup, so a finished workgroup's successor starts at once.
-  constexpr bool kPersistent = MODE == kApply && !LAST;
+  constexpr bool kPersistent = MODE == kApply && !LAST && KG == 1;
   const int xcds = g.xcds;
   const int xcd = bid % xcds;
   const int count = kconst(g.split)->count[xcd];
@@ -1120,7 +1142,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // Lane-derived values are recomputed for every tile (the empty asm keeps
   // the compiler from hoisting them out of the tile loop, where they would
   // stay live, in registers, through the epilogue).
-  int tid = threadIdx.x;
+  int tid = KG == 1 ? int(threadIdx.x) : int(threadIdx.x) - kg * kNT;
   if constexpr (kPersistent) asm volatile("" : "+v"(tid));
   __builtin_assume(tid >= 0 && tid < kNT);
 
@@ -1177,17 +1199,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     if (MODE == kGram) {
       o.a = o.b = at(xcur);
       o.lda = o.ldb = m.l_pad;
-      o.K = int(m.l_pad);
+      o.K = (m.l + kBK - 1) / kBK * kBK;
     } else if (MODE == kPoly) {
       o.a = o.b = at(m.off_a);
       o.lda = o.ldb = m.s_pad;
-      o.K = int(m.s_pad);
+      o.K = (m.s + kBK - 1) / kBK * kBK;
     } else {
       o.a = at(m.off_b);
       o.b = at(xcur);
       o.lda = m.s_pad;
       o.ldb = m.l_pad;
-      o.K = int(m.s_pad);
+      o.K = (m.s + kBK - 1) / kBK * kBK;
     }
     o.a += int64_t(t.tm) * BT * o.lda;
     o.b += kBRows ? int64_t(t.tn) * BT : int64_t(t.tn) * BT * o.ldb;
@@ -1196,7 +1218,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     o.b_off = kBRows
         ? uint32_t(((dw * kRpiB + lane / kChunksB) * o.ldb + ((lane % kChunksB) ^ swb(dw * kRpiB + lane / kChunksB)) * kEpc) * sizeof(T))
         : uint32_t(((dw * 8 + (lane >> 3)) * o.ldb + ((lane & 7) ^ swz(dw * 8 + (lane >> 3))) * kEpc) * sizeof(T));
-    o.same = MODE != kApply && sizeof(T) == 2 && t.tm == t.tn;
+    o.same = MODE != kApply && sizeof(T) == 2 && kNBuf == 2 && t.tm == t.tn;
     return o;
   };
   // One 16-byte-per-lane copy in the scalar-base form: wave-uniform base
@@ -1232,7 +1254,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     }
   };
   constexpr int kOps = kInst + (kBRows ? kInstB : kInst);   // copies per issuing wave per stage
-  static_assert(kDirect + (kNBuf - 1) * kOps < 64, "outstanding vector memory operations fit the counter");
+  static_assert((kPersistent ? kDirect : 0) + (kNBuf - 1) * kOps < 64, "outstanding vector memory operations fit the counter");
   const auto& task = tasks[slot];
   const auto& mm = kconst(g.mats)[task.mat];
   const int64_t off_x_nxt = g.src ? mm.off_x[0] : mm.off_x[1];
@@ -1403,7 +1425,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 
   // The barrier after each stage both publishes the stage just loaded (every
   // wave has waited for its own loads) and frees the buffer just read.
-  const int nk = K / kBK;
+  const int nk_all = K / kBK;
+  const int nk = (nk_all - kg + KG - 1) / KG;      // this group's stages
+  const int nk_max = (nk_all + KG - 1) / KG;
   // Wait until stage `s` has landed when `later` stages were requested after
   // it (and, for a prefetched first stage, this wave's stores in between).
   auto wait_stage = [&](int later, bool stores) {
@@ -1411,36 +1435,27 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
       if (stores) wait_vmcnt<kDirect>();
       else wait_vmcnt<0>();
     } else {
-      static_assert(kNBuf == 4, "stage waits written out for 2 or 4 buffers");
-      // the counts assume kOps copies per stage: a diagonal tile of a
-      // symmetric product copies one operand only
-      static_assert(MODE == kApply, "four stages only for the apply");
+      // (every stage has kOps copies: with more than two buffers a diagonal
+      // tile of a symmetric product copies both operands)
       const int n = later < kNBuf - 2 ? later : kNBuf - 2;
-      if (stores) {
-        if (n >= 2) wait_vmcnt<kDirect + 2 * kOps>();
-        else if (n == 1) wait_vmcnt<kDirect + kOps>();
-        else wait_vmcnt<kDirect>();
-      } else {
-        if (n >= 2) wait_vmcnt<2 * kOps>();
-        else if (n == 1) wait_vmcnt<kOps>();
-        else wait_vmcnt<0>();
-      }
+      if (stores) wait_stages<kNBuf - 2, kOps, kDirect>(n);
+      else wait_stages<kNBuf - 2, kOps, 0>(n);
     }
   };
   // stages 0 .. kNBuf - 2 in flight before the first MFMA (stage 0 may have
   // been requested already, during the previous tile's last K stage)
-  if (!prefetched) dma(ops, base, 0);
+  if (!prefetched && (KG == 1 || nk > 0)) dma(ops, base, kg * kBK);
 #pragma unroll
   for (int st = 1; st < kNBuf - 1; ++st)
-    if (st < nk) dma(ops, (base + st) & (kNBuf - 1), st * kBK);
-  wait_stage(nk - 1, prefetched);
+    if (st < nk) dma(ops, (base + st) & (kNBuf - 1), (st * KG + kg) * kBK);
+  wait_stage(nk > 0 ? nk - 1 : 0, prefetched);
   prefetched = false;
   lds_barrier();
   // persistent apply: the next tile's first stage is requested at the start
   // of this tile's last stage, into the buffer no stage of this tile uses
   // then, so that it lands during that stage and the epilogue
   const int nslot = live(slot + step);
-  for (int kt = 0; kt < nk; ++kt) {
+  for (int kt = 0; kt < nk_max; ++kt) {
     const int buf = (base + kt) & (kNBuf - 1);
     // the next stage's copies go out first, into the buffer of stage kt - 1,
     // which every wave finished before the barrier that ended the previous
@@ -1448,17 +1463,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     // then overlaps this stage's transpose reads (an assembly block: the
     // compiler adds no wait for the copies before it)
     const int nxt = kt + kNBuf - 1;
-    if (nxt < nk) dma(ops, (base + nxt) & (kNBuf - 1), nxt * kBK);
+    if (nxt < nk) dma(ops, (base + nxt) & (kNBuf - 1), (nxt * KG + kg) * kBK);
     if (kPersistent && kt == nk - 1 && nslot < count) {
       dma(make_ops(tasks[nslot]), (base + nk) & (kNBuf - 1), 0);
       prefetched = true;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (kTrB) {
-      preload_b(buf);
-      __builtin_amdgcn_sched_barrier(0);
+    if (KG == 1 || kt < nk) {
+      if constexpr (kTrB) {
+        preload_b(buf);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      compute(buf);
     }
-    compute(buf);
     __builtin_amdgcn_sched_barrier(0);
     // stage kt + 1 (after the last stage nothing: the next tile's first
     // stage stays in flight)
@@ -1468,6 +1485,39 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // (the barrier after the last stage means no wave reads the operand
   // buffers any more)
   if (kPersistent) base = (base + nk) & (kNBuf - 1);
+  if constexpr (KG > 1) {
+    // the groups' sums, in group order; only group 0 goes on to the epilogue
+    // (a barrier waits only for the waves still running)
+    static_assert((KG - 1) * BT * BT * 4 <= L::kBytes, "sums fit the operand buffers");
+    f32x4* sums = reinterpret_cast<f32x4*>(smem);
+    auto at_sum = [&](int g2, int i, int j, int q) {
+      return sums + ((((g2 - 1) * kMI + i) * kNI + j) * 4 + q) * kNT + tid;
+    };
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < kMI; ++i)
+#pragma unroll
+        for (int j = 0; j < kNI; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *at_sum(kg, i, j, q) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    }
+    lds_barrier();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g2 = 1; g2 < KG; ++g2)
+#pragma unroll
+      for (int i = 0; i < kMI; ++i)
+#pragma unroll
+        for (int j = 0; j < kNI; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = *at_sum(g2, i, j, q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+          }
+    lds_barrier();
+  }
 
   // ---- epilogues ----------------------------------------------------------
   // The Gram and polynomial results leave through LDS: each lane writes its
@@ -1722,25 +1772,26 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 }
 
 // One entry point per Newton-Schulz product, so profiles name each stage.
-template <typename T, int BT>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads) void ns_gram_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kGram, BT>::kBytes];
-  gemm_body<T, kGram, BT>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+// NB: LDS stages, 0 for the usual number of the tile.
+template <typename T, int BT, int NB = 0, int KG = 1>
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_gram_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kGram, BT, NB, KG>::kBytes];
+  gemm_body<T, kGram, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads) void ns_poly_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kPoly, BT>::kBytes];
-  gemm_body<T, kPoly, BT>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0, int KG = 1>
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_poly_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kPoly, BT, NB, KG>::kBytes];
+  gemm_body<T, kPoly, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads) void ns_apply_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT>::kBytes];
-  gemm_body<T, kApply, BT>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0, int KG = 1>
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_apply_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
+  gemm_body<T, kApply, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads) void ns_apply_last_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT>::kBytes];
-  gemm_body<T, kApply, BT, true>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0, int KG = 1>
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_apply_last_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
+  gemm_body<T, kApply, BT, true, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
 // An apply step's 256-tiles and the small tiles of its last round in one
 // launch: the first `main_grid` workgroups run the 256-tiles, the rest the
@@ -1845,11 +1896,10 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
   a.wd = l.wd;
   a.decide = l.decide;
   // persistent: at most as many workgroups per XCD as its CUs hold at once,
-  // limited by LDS (256-tiles: one per CU; 128-tiles: two, or one for the
-  // four-stage bf16 apply; 64-tiles: four, or two for the bf16 apply)
-  // (only the non-final apply is persistent; the others keep one workgroup
-  // per tile)
-  const int per_cu = l.tile == 256 ? 1 : (l.tile == 128 ? (l.fp32 ? 2 : 1) : (l.fp32 ? 4 : 2));
+  // limited by LDS (256-tiles: one per CU; two-stage 128-tiles: two;
+  // two-stage 64-tiles: four). Only the non-final apply is persistent; the
+  // others keep one workgroup per tile.
+  const int per_cu = l.tile == 256 ? 1 : (l.tile == 128 ? 2 : 4);
   const int per_xcd = (mode != kApply || l.last) ? l.max_count : (l.chip.cus / l.chip.xcds) * per_cu;
   const dim3 grid(unsigned(l.max_count < per_xcd ? l.max_count : per_xcd) * unsigned(l.chip.xcds));
 #define LM_LAUNCH(KERNEL, T, BT) \
@@ -1892,13 +1942,34 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
     } else {
       LM_LAUNCH_MODE(bf16, 256);
     }
-  } else if (l.tile == 128) {
-    LM_LAUNCH_MODE(bf16, 128);
   } else {
-    // bf16 64-tiles exist for the apply only (the last round of 256-tiles)
-    if (l.tile != 64 || mode != kApply) return hipErrorInvalidValue;
-    if (!l.last) LM_LAUNCH(ns_apply_kernel, bf16, 64);
-    else LM_LAUNCH(ns_apply_last_kernel, bf16, 64);
+    // one workgroup per tile, except the persistent apply
+    const dim3 full(unsigned(l.max_count) * unsigned(l.chip.xcds));
+#define LM_LAUNCH_SYM(BT, NB, KG)                                                                  \
+  do {                                                                                             \
+    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
+    if (mode == kGram) hipLaunchKernelGGL((ns_gram_kernel<bf16, BT, NB, KG>), full, block, 0, stream, a); \
+    else hipLaunchKernelGGL((ns_poly_kernel<bf16, BT, NB, KG>), full, block, 0, stream, a);        \
+  } while (0)
+#define LM_LAUNCH_APPLY(BT, NB)                                                                    \
+  do {                                                                                             \
+    const dim3 block(TileGeom<BT>::kThreads);                                                      \
+    if (!l.last) hipLaunchKernelGGL((ns_apply_kernel<bf16, BT, NB>), grid, block, 0, stream, a);   \
+    else hipLaunchKernelGGL((ns_apply_last_kernel<bf16, BT, NB>), full, block, 0, stream, a);      \
+  } while (0)
+    if (mode == kApply) {
+      if (l.tile == 128 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_APPLY(128, 2);
+      else if (l.tile == 64 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_APPLY(64, 2);
+      else return hipErrorInvalidValue;
+    } else {
+      if (l.tile == 128 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_SYM(128, 2, 1);
+      else if (l.tile == 64 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_SYM(64, 2, 1);
+      else if (l.tile == 64 && l.bufs == 4 && l.groups == 1) LM_LAUNCH_SYM(64, 4, 1);
+      else if (l.tile == 64 && l.bufs == 4 && l.groups == 2) LM_LAUNCH_SYM(64, 4, 2);
+      else return hipErrorInvalidValue;
+    }
+#undef LM_LAUNCH_SYM
+#undef LM_LAUNCH_APPLY
   }
 #undef LM_LAUNCH_MODE
 #undef LM_LAUNCH

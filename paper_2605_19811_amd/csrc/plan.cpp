@@ -4,8 +4,10 @@
 #include <algorithm>
 #include <cstdint>
 #include <cmath>
+#include <functional>
 #include <map>
 #include <numeric>
+#include <queue>
 #include <utility>
 
 namespace lm {
@@ -84,7 +86,155 @@ int32_t pick_sym_tile(const std::vector<MuonMat>& mats, bool gram, ChipShape chi
   return est[0] <= est[1] ? kTileBig : kTileSmall;
 }
 
+// Tiles of `tile` over the rows and columns that hold matrix data (the
+// padding past them is never read: K loops end at the same place), costs =
+// K stages of 64. `sym`: the lower triangle of the s x s output.
+void fine_tiles(const std::vector<MuonMat>& mats, int fp32, int st, int tile,
+                std::vector<GemmTask>* tasks, std::vector<int64_t>* cost) {
+  for (int32_t mi = 0; mi < int32_t(mats.size()); ++mi) {
+    const MuonMat& mm = mats[size_t(mi)];
+    if (mm.fp32 != fp32) continue;
+    const int ts = (mm.s + tile - 1) / tile, tl = (mm.l + tile - 1) / tile;
+    const int64_t stages = ((st == 0 ? mm.l : mm.s) + 63) / 64;
+    if (st == 2) {
+      for (int tn = 0; tn < tl; ++tn)
+        for (int tm = 0; tm < ts; ++tm) {
+          tasks->push_back({mi, int16_t(tm), int16_t(tn)});
+          cost->push_back(stages);
+        }
+      continue;
+    }
+    // the lower triangle in blocks of 512 x 512, so that the tiles an XCD
+    // runs at one time share their row panels in its L2
+    const int nb = 512 / tile;
+    for (int bm = 0; bm < ts; bm += nb)
+      for (int bn = 0; bn <= bm; bn += nb)
+        for (int tm = bm; tm < std::min(bm + nb, ts); ++tm)
+          for (int tn = bn; tn < std::min(bn + nb, tm + 1); ++tn) {
+            tasks->push_back({mi, int16_t(tm), int16_t(tn)});
+            cost->push_back(stages);
+          }
+  }
+}
+
+// Estimated time (units of 10 ns, past what every launch costs) of one
+// launch: each XCD's tiles, longest first, go to its least loaded CU, which
+// runs `slots` of them at a time. A K stage takes `alone` in a workgroup that
+// has its CU to itself (latency), and `shared` of the CU's time where several
+// compete for its operand traffic; `fixed` is a tile's start and epilogue.
+// The constants were fitted to bf16 launches over lists of 1 to 48 matrices
+// with short sides of 128 to 2048 (agreement within 15%).
+struct StageCost {
+  int64_t alone, shared, fixed;
+};
+int64_t launch_estimate(const std::vector<int64_t>& stages, const XcdSplit& split, int slots,
+                        StageCost c, ChipShape chip) {
+  struct Cu {
+    int64_t load, sum, longest, done;   // stages assigned; the current group's; finished groups' time
+    int n;
+  };
+  const int cus = std::max(1, chip.cus / chip.xcds);
+  auto group = [&](const Cu& u) {
+    return u.n == 0 ? 0 : std::max(u.longest * c.alone, u.sum * c.shared) + c.fixed;
+  };
+  int64_t worst = 0;
+  for (int x = 0; x < chip.xcds; ++x) {
+    auto more = [](const Cu& a, const Cu& b) { return a.load > b.load; };
+    std::priority_queue<Cu, std::vector<Cu>, decltype(more)> q(more);
+    for (int i = 0; i < cus; ++i) q.push(Cu{0, 0, 0, 0, 0});
+    for (int32_t i = split.start[x]; i < split.start[x] + split.count[x]; ++i) {
+      Cu u = q.top();
+      q.pop();
+      if (u.n == slots) {
+        u.done += group(u);
+        u.sum = u.longest = u.n = 0;
+      }
+      const int64_t k = stages[size_t(i)];
+      u.load += k;
+      u.sum += k;
+      u.longest = std::max(u.longest, k);
+      ++u.n;
+      q.push(u);
+    }
+    for (; !q.empty(); q.pop()) worst = std::max(worst, q.top().done + group(q.top()));
+  }
+  return worst;
+}
+
+// The K stages of a split list's tasks, in list order.
+std::vector<int64_t> stages_of(const std::vector<MuonMat>& mats, const std::vector<GemmTask>& tasks,
+                               int st) {
+  std::vector<int64_t> c(tasks.size());
+  for (size_t i = 0; i < tasks.size(); ++i) {
+    const MuonMat& mm = mats[size_t(tasks[i].mat)];
+    c[i] = ((st == 0 ? mm.l : mm.s) + 63) / 64;
+  }
+  return c;
+}
+
+// Small tiles for one bf16 product (st: Gram, polynomial, apply) where they
+// are estimated to beat the tiles already chosen (`p->tile`), which fill the
+// chip on the large sets but leave most of it idle on a shard or a small
+// model: one 768 x 3072 matrix is 36 apply 256-tiles on 256 CUs. Measured
+// (us a launch, the usual tiles -> these): one 768 x 3072 matrix Gram 42 -> 14,
+// polynomial 15 -> 8, apply 28 -> 12; the four matrices of a 768-wide layer
+// 42 -> 19, 15 -> 9, 29 -> 18; sixteen 256 x 1024 15 -> 7, 9 -> 5, 18 -> 9. At
+// two layers the apply's 256-tiles are level (31 against 34), at four all
+// three are; at twelve 64-tiles lose (Gram 86 -> 130, apply 168 -> 300).
+void pick_fine(Plan* p, int st) {
+  const std::vector<GemmTask>& macro = st == 0 ? p->gram[0] : (st == 1 ? p->poly[0] : p->apply[0]);
+  const size_t cus = size_t(p->chip.cus);
+  if (macro.empty() || macro.size() >= 8 * cus || p->chip.cus < p->chip.xcds) return;
+  struct Choice {
+    GemmVariant v;
+    StageCost c;
+    bool one_round;        // only where every tile gets a CU of its own
+  };
+  static const Choice sym[] = {{{64, 4, 2, 1}, {20, 20, 150}, true},
+                               {{64, 4, 1, 2}, {27, 20, 150}, false},
+                               {{64, 2, 1, 4}, {46, 20, 150}, false},
+                               {{128, 2, 1, 2}, {78, 62, 250}, false}};
+  static const Choice app[] = {{{64, 2, 1, 4}, {46, 19, 150}, false},
+                               {{128, 2, 1, 2}, {85, 55, 300}, false}};
+  const StageCost big = st < 2 ? StageCost{150, 150, 500} : StageCost{200, 200, 400};
+  const XcdSplit& msplit = st == 0 ? p->gram_split[0] : (st == 1 ? p->poly_split[0] : p->apply_split[0]);
+  int64_t best = 0;
+  if (p->tile[0][st] == kTileBig) {
+    best = launch_estimate(stages_of(p->mats, macro, st), msplit, 1, big, p->chip);
+    // the apply's first start and last store, and the last round's small tiles
+    if (st == 2) best += p->apply_tail[0].empty() ? 300 : 600;
+  } else {
+    best = launch_estimate(stages_of(p->mats, macro, st), msplit, 2, sym[3].c, p->chip);
+  }
+  for (const Choice* k = st < 2 ? sym : app; k != (st < 2 ? sym + 4 : app + 2); ++k) {
+    const GemmVariant v = k->v;
+    const StageCost c = k->c;
+    std::vector<GemmTask> tasks;
+    std::vector<int64_t> cost;
+    fine_tiles(p->mats, 0, st, v.tile, &tasks, &cost);
+    if (k->one_round && tasks.size() > cus) continue;
+    XcdSplit split;
+    split_by_xcd(&tasks, cost, p->chip.xcds, &split);
+    const int64_t est = launch_estimate(stages_of(p->mats, tasks, st), split, v.slots, c, p->chip);
+    // 8% less, or the tiles stay as they are: about the spread between boxes
+    if (est * 108 >= best * 100) continue;
+    best = est;
+    p->variant[0][st] = v;
+    p->fine[0][st].swap(tasks);
+    p->fine_split[0][st] = split;
+  }
+}
+
 }  // namespace
+
+void drop_fine(Plan* p) {
+  for (int pr = 0; pr < 2; ++pr)
+    for (int st = 0; st < 3; ++st) {
+      p->fine[pr][st].clear();
+      p->fine_split[pr][st] = XcdSplit{};
+      p->variant[pr][st] = GemmVariant{};
+    }
+}
 
 int sr_tall_bucket(int64_t s) {
   const int64_t n = (s + 255) / 256;
@@ -412,6 +562,7 @@ Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
     split_by_xcd(&p->apply[pr], ca, chip.xcds, &p->apply_split[pr]);
     split_by_xcd(&p->apply_tail[pr], ct, chip.xcds, &p->apply_tail_split[pr]);
   }
+  for (int st = 0; st < 3; ++st) pick_fine(p, st);
 
   size_t off = align256(size_t(ns_off));
   p->ws_partials_off = off;

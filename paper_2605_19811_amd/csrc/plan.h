@@ -54,6 +54,12 @@ struct NsPrecision {
 // Appendix G made on the device.
 enum class StepKind : int { kLion = 0, kMuon = 1, kAdaptive = 2 };
 
+// One way to run a product in small tiles: tile edge, LDS stages, and groups
+// of waves that share a tile's K loop. `slots` such workgroups fit a CU.
+struct GemmVariant {
+  int32_t tile = 0, bufs = 2, groups = 1, slots = 1;
+};
+
 struct Plan {
   bool muon_step = false;
   bool adaptive = false;
@@ -79,6 +85,12 @@ struct Plan {
   // the same launch as `apply`
   std::vector<GemmTask> apply_tail[2];
   XcdSplit apply_tail_split[2]{};
+  // What the launches run in place of gram, poly and apply where that is
+  // estimated to be faster (`variant[..].tile` > 0): the same products in
+  // smaller tiles, over the rows and columns that hold the matrix only.
+  std::vector<GemmTask> fine[2][3];
+  XcdSplit fine_split[2][3]{};
+  GemmVariant variant[2][3]{};
   int32_t tile[2][3] = {{kTileBig, kTileBig, kTileBig}, {kTileSmall, kTileSmall, kTileSmall}};
   int32_t tail_tile[2] = {kTileSmall, kTileSmall};   // tile edge of apply_tail
   int64_t muon_elements = 0;
@@ -120,6 +132,10 @@ Status validate_tensors(const TensorIn* x, int32_t n, std::string* err);
 // does not depend on alignment either.
 Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
                   bool kappa_rms02, ChipShape chip, Plan* out, std::string* err);
+
+// Take the small-tile lists out of a plan (the launches then run gram, poly
+// and apply).
+void drop_fine(Plan* p);
 
 // 16-byte alignment class of one tensor's buffers (the only property of its
 // addresses a plan depends on): bit 0 = W, G, M (and V for AdamW) all 16-byte

@@ -1,0 +1,64 @@
+"""Products in small tiles (lists that leave the chip idle at the usual ones).
+
+CPU: the planner's choice and its tile lists (``planner_small_tiles_driver.cpp``).
+GPU: Muon steps over the same lists against the oracle, at sides on both
+sides of a tile edge and K loops of one stage, of fewer stages than a tile has
+LDS buffers, and of an odd number for two wave groups.
+"""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2605_19811_amd", "csrc")
+
+# list of shapes -> "tile/LDS stages/wave groups" of Gram, polynomial, apply
+# (0: the usual tiles)
+LISTS = {
+    "one-stage": ([(64, 64)], "64/4/2 64/4/2 64/2/1"),
+    "edges": ([(65, 129), (129, 65), (127, 193), (64, 321)], "64/4/2 64/4/2 64/2/1"),
+    "one-wide": ([(300, 1000)], "64/4/2 64/4/2 64/2/1"),
+    "one-tall": ([(1089, 257)], "64/4/2 64/4/2 64/2/1"),
+    "two-per-cu": ([(500, 700), (700, 500)] * 5, "64/4/1 64/4/1 64/2/1"),
+    "apply-128": ([(768, 2304), (768, 768), (768, 3072), (3070, 766)], "64/4/1 64/4/1 128/2/1"),
+    "poly-two-stage": ([(2000, 2000)], "64/2/1 64/2/1 64/2/1"),
+    "gram-small-only": ([(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 3, "64/4/1 0/2/1 0/2/1"),
+}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_planner_small_tile_lists(tmp_path):
+    exe = str(tmp_path / "small_tiles")
+    subprocess.run(["g++", "-O1", "-std=c++17", f"-I{CSRC}",
+                    os.path.join(HERE, "planner_small_tiles_driver.cpp"),
+                    os.path.join(CSRC, "plan.cpp"), "-o", exe], check=True)
+    for name, (shapes, variants) in LISTS.items():
+        args = [str(v) for s in shapes for v in s]
+        run = subprocess.run([exe, *args], capture_output=True, text=True)
+        assert run.returncode == 0 and run.stdout.split("bad")[0].strip() == variants, (name, run.stdout)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(LISTS))
+def test_small_tiles_match_oracle(name):
+    import torch
+
+    from paper_2605_19811_amd import lionmuon as lm
+    from parity import check_muon
+    shapes = LISTS[name][0]
+    rng = np.random.default_rng(len(shapes) + shapes[0][0])
+    W0, M0, G = ([(rng.standard_normal(s) * std).astype(np.float32) for s in shapes]
+                 for std in (0.02, 1e-2, 1e-2))
+    W, M, Gd = ([torch.from_numpy(x).cuda() for x in t] for t in (W0, M0, G))
+    cfg = lm.config(lr_muon=0.02)
+    # a workspace of NaN: what no kernel of the call writes must not be read
+    ws = torch.full((lm.lionmuon_workspace_bytes([(*s, False) for s in shapes], cfg),), 0xFF,
+                    dtype=torch.uint8, device="cuda")
+    lm.lionmuon_step_ex(W, Gd, M, 0, 1, 0.9, 0.99, 0.1, cfg, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(len(shapes)):
+        check_muon(W0[i], G[i], M0[i], W[i].cpu().double().numpy(), M[i].cpu().double().numpy(),
+                   0.9, 0.99, 0.02, 0.1, "bf16")
