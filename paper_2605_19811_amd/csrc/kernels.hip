@@ -30,6 +30,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
@@ -1018,6 +1019,17 @@ __device__ __forceinline__ void sched_interleave() {
   }
 }
 
+// N times one MFMA, then V vector operations and R LDS reads.
+template <int N, int V, int R>
+__device__ __forceinline__ void sched_split() {
+  if constexpr (N > 0) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    if constexpr (R > 0) __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
+    sched_split<N - 1, V, R>();
+  }
+}
+
 template <typename T> struct Mfma;
 
 template <> struct Mfma<bf16> {
@@ -1032,13 +1044,54 @@ template <> struct Mfma<bf16> {
   }
 };
 
+// fp32 products on the bf16 matrix instruction: each fp32 operand x is the
+// exact sum of three bf16 values, x = h + m + l, the upper, middle and lower
+// eight bits of its significand, and the product keeps the six terms down to
+// 2^-16 of the largest (hh; hm, mh; hl, lh, mm), so what it drops (ml, lm, ll)
+// is at most 2^-22 (typically 2^-25) of a term, below the rounding of an fp32
+// product. Six 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32
+// ones took 512. The operands stay fp32 in memory and in LDS and are split in
+// registers (44 vector operations a fragment).
 template <> struct Mfma<float> {
   static constexpr int kBK = 32;
-  static constexpr int kKStep = 2;
-  typedef float Frag;
-  __device__ static __forceinline__ Frag load(const float* row, int lk) { return row[lk]; }
-  __device__ static __forceinline__ f32x16 mma(Frag a, Frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  static constexpr int kKStep = 16;
+  struct Frag {
+    u32x4 h, m, l;
+  };
+  // Eight values of a lane. Each part is the upper 16 bits of what is left of
+  // the value (truncated, so the remainder is exact).
+  __device__ static __forceinline__ Frag split(const float x[8]) {
+    Frag f;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      uint32_t u[2], v[2], w[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        u[e] = __builtin_bit_cast(uint32_t, x[2 * p + e]);
+        const float r = x[2 * p + e] - __builtin_bit_cast(float, u[e] & 0xffff0000u);
+        v[e] = __builtin_bit_cast(uint32_t, r);
+        w[e] = __builtin_bit_cast(uint32_t, r - __builtin_bit_cast(float, v[e] & 0xffff0000u));
+      }
+      f.h[p] = __builtin_amdgcn_perm(u[1], u[0], 0x07060302u);
+      f.m[p] = __builtin_amdgcn_perm(v[1], v[0], 0x07060302u);
+      f.l[p] = __builtin_amdgcn_perm(w[1], w[0], 0x07060302u);
+    }
+    return f;
+  }
+  __device__ static __forceinline__ f32x16 mul(u32x4 a, u32x4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+  static constexpr int kTerms = 6;
+  // the terms from the smallest on
+  __device__ static __forceinline__ f32x16 term(int t, const Frag& a, const Frag& b, f32x16 c) {
+    switch (t) {
+      case 0: return mul(a.l, b.h, c);
+      case 1: return mul(a.h, b.l, c);
+      case 2: return mul(a.m, b.m, c);
+      case 3: return mul(a.m, b.h, c);
+      case 4: return mul(a.h, b.m, c);
+      default: return mul(a.h, b.h, c);
+    }
   }
 };
 
@@ -1075,10 +1128,228 @@ struct GemmLds {
   // them in flight while one feeds the MFMAs.
   // NB > 0 sets the count (64-tiles of lists that leave CUs idle).
   static constexpr int kNBuf = NB > 0 ? NB : (sizeof(T) == 2 && (BT == 64 || (MODE == kApply && BT == 128))) ? 4 : 2;
-  static constexpr int kOperand = kNBuf * KG * 2 * BT * kLd, kStage = BT * kStR;
+  // fp32: four stages (128-tiles: two) of 16 KB an operand (split_product)
+  static constexpr int kOperand = sizeof(T) == 4 ? (BT == 128 ? 2 : 4) * 2 * 128 * 32 : kNBuf * KG * 2 * BT * kLd, kStage = BT * kStR;
   static constexpr int kElems = kOperand > kStage ? kOperand : kStage;
   static constexpr int kBytes = kElems * int(sizeof(T));
 };
+
+template <int V> struct Const {
+  static constexpr int value = V;
+};
+
+// Operands of one tile.
+template <typename T> struct GemmOps {
+  const T* a;
+  const T* b;
+  int64_t lda, ldb;
+  int K;
+  uint32_t a_off, b_off;
+  bool same;                                   // symmetric product, diagonal tile: B rows = A rows
+};
+
+// One 16-byte-per-lane copy to LDS in the scalar-base form: wave-uniform base
+// address and LDS destination (M0, one wait state after writing it) in
+// scalar registers, one 32-bit offset per lane. Written as an assembly
+// block: from the builtin, inside the K loop, the compiler formed 64-bit
+// per-lane addresses and moved M0 from vector registers for every copy
+// (apply 2-5%, polynomial 5% slower). The compiler neither counts these
+// copies nor waits for them: every wait for them is explicit.
+// M0 is reserved to the compiler, which does not track the clobber; no
+// other code in these kernels uses M0.
+template <typename T>
+__device__ __forceinline__ void copy16(const T* src, uint32_t off, const T* dst) {
+  const uint32_t d = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const T*)(dst)));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(off), "s"(src), "s"(d) : "memory", "m0");
+}
+
+// K loop of one fp32 tile by four waves, each accumulating 64 x 64 (2 x 2 MFMA
+// blocks): on a 128-tile a wave has its quadrant and stages are 32 K values;
+// on a 64-tile every wave has the whole tile and a quarter of each stage of 64
+// (their sums meet in LDS at the end). Either way a stage is 16 KB an operand,
+// copied two or three stages ahead to a ring of LDS buffers (two for 128-tiles, so
+// that two workgroups fit a CU): 128 rows of 32 values (64-tile: the
+// rows of K 0..31, then those of K 32..63), chunks swizzled as for bf16, or, for
+// the apply's X, rows of K. The vector operations of the split bound this
+// loop, so a fragment has to serve two MFMA blocks: with 32 x 32 to a wave a 768 x 768
+// product took 21 us (15 now; fp32 MFMAs on 64-tiles 23), and with the values split
+// once, on their way into LDS, 18-22. Up to six vector operations between two MFMAs
+// cost nothing, all of them in one place their full time (measured), hence
+// `order`. Each K step's fragments are read and split while the MFMAs of the
+// step before run, which the barrier in mid-stage
+// allows (it publishes the next stage). The matrix unit truncates where it adds
+// to its accumulator: the products of each 128 K values start from zero, and
+// vector adds collect them (1000 x 3000 matrix, five steps: 1.1e-6 from 64 bits,
+// 1.0e-5 with one accumulator over the whole K loop, 3.3e-6 by fp32 MFMAs). Two
+// 1000 x 3000: Gram 109 -> 81 us, apply 135 -> 89.
+template <int MODE, int BT>
+__device__ __forceinline__ void split_product(const GemmOps<float>& o, float* smem, int tid, f32x16 (&out)[BT / 64][BT / 64]) {
+  using M = Mfma<float>;
+  constexpr int kBuf = BT == 128 ? 2 : 4, kAhead = BT == 128 ? 2 : 3, kOperand = 4096, kStage = 2 * kOperand;   // floats
+  constexpr int kStageK = BT == 128 ? 32 : 64, kSub = BT == 128 ? 2 : 1;
+  constexpr bool kBCols = MODE == kApply;        // B is X, K along its rows
+  constexpr int kChunks = BT / 4, kRpi = 64 / kChunks;   // its 16-byte chunks a row, rows a copy
+  const int lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nk = (o.K + kStageK - 1) / kStageK;
+  auto swz = [](int row) { return (row & 7) ^ ((row >> 3) & 1); };
+  auto swb = [](int k) { return (k & 3) * 4; };
+  const int crow = wave * 8 + (lane >> 3), cchunk = ((lane & 7) ^ swz(crow)) * 4;
+  const int krow = wave * kRpi + lane / kChunks;
+  const uint32_t oa = uint32_t((crow * o.lda + cchunk) * 4);
+  const uint32_t ob = uint32_t((kBCols ? krow * o.ldb + ((lane % kChunks) ^ swb(krow)) * 4 : crow * o.ldb + cchunk) * 4);
+  auto copy_rows = [&](const float* p, int64_t ld, uint32_t off, float* dst) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      copy16(BT == 128 ? p + 32 * q * ld : p + 32 * (q & 1) * ld + 32 * (q >> 1), off, dst + (q * 32 + wave * 8) * 32);
+  };
+  auto copy = [&](int kt) {
+    // (past the end the last stage again, into a buffer nobody uses: a branch
+    // here would cut the block of code that `order` schedules)
+    const int64_t k0 = int64_t(min(kt, nk - 1)) * kStageK;
+    float* a = smem + (kt & (kBuf - 1)) * kStage;
+    copy_rows(o.a + k0, o.lda, oa, a);
+    if constexpr (kBCols) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        copy16(o.b + (k0 + q * 4 * kRpi) * o.ldb, ob, a + kOperand + (q * 4 + wave) * kRpi * BT);
+    } else {
+      copy_rows(o.b + k0, o.ldb, ob, a + kOperand);
+    }
+  };
+  const int wa = (wave >> 1) * 64;               // the wave's rows of A: its tile rows, or its K half
+  const int wb = BT == 128 ? (wave & 1) * 64 : wa;
+  const int kstep = BT == 128 ? 0 : (wave & 1);  // the wave's K step of those rows (64-tile)
+  auto split_row = [&](const float* rows, int row, int step) {
+    const int c = step * 4 + lk * 2;
+    float x[8];
+    load4(rows + row * 32 + ((c ^ swz(row)) << 2), x);
+    load4(rows + row * 32 + (((c + 1) ^ swz(row)) << 2), x + 4);
+    return M::split(x);
+  };
+  auto split_col = [&](const float* rows, int n, int k0) {
+    float x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int k = k0 + 8 * lk + t;
+      x[t] = rows[k * BT + (((n >> 2) ^ swb(k)) << 2) + (n & 3)];
+    }
+    return M::split(x);
+  };
+  M::Frag fa[2][2], fb[2][2];                    // [parity of the step][block]
+  auto fetch = [&](int slot, int kt, int kk) {
+    const float* a = smem + (kt & (kBuf - 1)) * kStage;
+    const float* b = a + kOperand;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      fa[slot][i] = split_row(a, wa + 32 * i + lr, kstep + kk);
+      if constexpr (!kBCols) fb[slot][i] = split_row(b, wb + 32 * i + lr, kstep + kk);
+      else if constexpr (BT == 128) fb[slot][i] = split_col(b, wb + 32 * i + lr, 16 * kk);
+      else fb[slot][i] = split_col(b, 32 * i + lr, 16 * wave);
+    }
+  };
+  f32x16 acc[2][2], part[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = part[i][j] = f32x16(0.0f);
+  auto fold = [&] {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] += part[i][j];
+  };
+  auto multiply = [&](int slot, auto fresh) {    // smallest terms first; four independent chains
+#pragma unroll
+    for (int t = 0; t < M::kTerms; ++t)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          part[i][j] = M::term(t, fa[slot][i], fb[slot][j], decltype(fresh)::value && t == 0 ? f32x16(0.0f) : part[i][j]);
+  };
+  auto order = [&] {                             // the fetch's reads, then its split between the MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x100, 40, 0);
+    sched_split<24, 8, 0>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Stage kt + 1 visible to every wave (with three stages ahead, stage kt + 2
+  // is still in flight). Then the request for stage kt + kAhead, into the buffer
+  // of a stage whose last reads every wave finished before this barrier.
+  auto next_stage = [&](int kt) {
+    wait_vmcnt<8 * (kAhead - 2)>();
+    lds_barrier();
+    copy(kt + kAhead);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto stage = [&](int par, int kt, auto fresh) {
+    if (decltype(fresh)::value) fold();
+    if constexpr (kSub == 2) {
+      fetch(1, kt, 1);
+      multiply(0, fresh);
+      order();
+      next_stage(kt);
+      fetch(0, kt + 1, 0);
+      multiply(1, Const<0>());
+      order();
+    } else {
+      next_stage(kt);
+      fetch(par ^ 1, kt + 1, 0);
+      multiply(par, fresh);
+      order();
+    }
+  };
+#pragma unroll
+  for (int st = 0; st < kAhead; ++st) copy(st);
+  wait_vmcnt<8 * (kAhead - 1)>();
+  lds_barrier();
+  fetch(0, 0, 0);
+  // rounds of 128 K values to a wave, each into `part` from zero; the tail of
+  // the last round one pair of stages at a time
+  constexpr int kRound = BT == 128 ? 4 : 8;
+  int kt = 0;
+  for (; kt + kRound <= nk; kt += kRound) {
+    stage(0, kt, Const<1>());
+#pragma unroll
+    for (int i = 1; i < kRound; ++i) stage(i & 1, kt + i, Const<0>());
+  }
+  if (kt < nk) stage(0, kt++, Const<1>());
+  for (; kt + 2 <= nk; kt += 2) {
+    stage(1, kt, Const<0>());
+    stage(0, kt + 1, Const<0>());
+  }
+  if (kt < nk) stage(1, kt, Const<0>());
+  fold();
+  wait_vmcnt<0>();                               // no copy may land in what follows
+  lds_barrier();
+  if constexpr (BT == 128) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) out[i][j] = acc[i][j];
+  } else {
+    // wave w keeps block w: the sum of the four waves' shares, in wave order
+    f32x4* sums = reinterpret_cast<f32x4*>(smem);
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x16& v = acc[blk >> 1][blk & 1];
+        sums[((blk * 4 + wave) * 4 + q) * 64 + lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v[w] = sums[((wave * 4 + w) * 4 + q) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[0][0][4 * q + e] = (v[0][e] + v[1][e]) + (v[2][e] + v[3][e]);
+    }
+    lds_barrier();
+  }
+}
 
 // LAST (apply only): the last Newton-Schulz step, whose epilogue updates W
 // (its own instantiation: that epilogue's registers would otherwise weigh
@@ -1104,7 +1375,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // K groups: the waves of group kg take every KG-th K stage, into buffers of
   // their own; their sums meet in LDS after the K loop.
   const int kg = KG == 1 ? 0 : int(__builtin_amdgcn_readfirstlane(threadIdx.x / kNT));
-  T* smem_g = smem + kg * (kNBuf * 2 * BT * kLd);
+  T* smem_g = smem + kg * (L::kOperand / KG);
   T (*sA)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g);
   T (*sB)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g + kNBuf * BT * kLd);
   // apply: the B operand (X, K = s along its rows) is staged k-major as
@@ -1119,7 +1390,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // registers, so the next tile's loads overlap them. The other products
   // stage their results through the whole LDS and run one tile per
   // workgroup, so a finished workgroup's successor starts at once.
-  constexpr bool kPersistent = MODE == kApply && !LAST && KG == 1;
+  constexpr bool kPersistent = MODE == kApply && !LAST && KG == 1 && sizeof(T) == 2;
   const int xcds = g.xcds;
   const int xcd = bid % xcds;
   const int count = kconst(g.split)->count[xcd];
@@ -1183,14 +1454,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // multiple of 4), the swizzle of a lane's row does not depend on the
   // instruction index.
   static_assert(kDmaWaves % 2 == 0 && (kDmaWaves * kRpiB) % 4 == 0, "swizzle independent of the instruction");
-  struct Ops {
-    const T* a;
-    const T* b;
-    int64_t lda, ldb;
-    int K;
-    uint32_t a_off, b_off;
-    bool same;                                   // symmetric product, diagonal tile: B rows = A rows
-  };
+  using Ops = GemmOps<T>;
   auto make_ops = [&](const __attribute__((address_space(4))) GemmTask& t) {
     const auto& m = kconst(g.mats)[t.mat];
     // ping-pong buffers chosen without indexing (keeps descriptors out of scratch)
@@ -1221,21 +1485,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     o.same = MODE != kApply && sizeof(T) == 2 && kNBuf == 2 && t.tm == t.tn;
     return o;
   };
-  // One 16-byte-per-lane copy in the scalar-base form: wave-uniform base
-  // address and LDS destination (M0, one wait state after writing it) in
-  // scalar registers, one 32-bit offset per lane. Written as an assembly
-  // block: from the builtin, inside the K loop, the compiler formed 64-bit
-  // per-lane addresses and moved M0 from vector registers for every copy
-  // (apply 2-5%, polynomial 5% slower). The compiler neither counts these
-  // copies nor waits for them: every wait for them is explicit (wait_stage).
-  // M0 is reserved to the compiler, which does not track the clobber; no
-  // other code in these kernels uses M0.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  auto copy16 = [&](const T* src, uint32_t off, const T* dst) {
-    const uint32_t d = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const T*)(dst)));
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(off), "s"(src), "s"(d) : "memory", "m0");
-  };
   auto dma = [&](const Ops& o, int buf, int k0) {
     if (wave_u >= kDmaWaves) return;
 #pragma unroll
@@ -1262,8 +1512,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   const int K = ops.K;
   // A bf16 diagonal tile of a symmetric product reads its B fragments from
   // the A operand's buffers (the same rows of X, or of A) and copies only
-  // those: Gram 3-4%, polynomial 2-4% faster at 124M-720M (the fp32 small
-  // tiles were 1% slower with it and keep both copies).
+  // those: Gram 3-4%, polynomial 2-4% faster at 124M-720M (fp32 copies both).
   T (*sBf)[BT][kLd] = ops.same ? sA : sB;
   const int row0 = task.tm * BT, col0 = task.tn * BT;
 
@@ -1275,19 +1524,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
+  const int nk_all = K / kBK;
+  const int nk = (nk_all - kg + KG - 1) / KG;      // this group's stages
+  const int nk_max = (nk_all + KG - 1) / KG;
+  const int nslot = live(slot + step);
+  if constexpr (sizeof(T) == 4) {
+    split_product<MODE, BT>(ops, smem, tid, acc);
+  } else {
   auto frag = [&](const T* rowp, int row, int kc) {
     const int e = kc + lk * (M::kKStep / 2);
     const int off = (((e / kEpc) ^ swz(row)) * kEpc) + (e % kEpc);
     return M::load(rowp + off, 0);
-  };
-  // B fragment of block column j from k-major rows: the MFMA wants, in lane
-  // (n = lane % 32, half lk), B[kc + lk kKStep/2 + t][n] for t < kKStep/2.
-  // fp32 apply: B fragment of block column j from the k-major rows (one
-  // element per lane: B[kc + lk][n]); the bf16 apply reads its fragments
-  // with transpose reads (preload_b below)
-  auto frag_b_rows = [&](int buf, int j, int kc) -> typename M::Frag {
-    const int k = kc + lk, n = wn + 32 * j + lr;
-    return sBr[buf][k][(((n >> 2) ^ swb(k)) << 2) + (n & 3)];
   };
   constexpr int kSub = kBK / M::kKStep;
   // bf16 apply: the B fragments of a whole stage are read into registers
@@ -1402,7 +1649,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 #pragma unroll
       for (int j = 0; j < kNI; ++j) {
         if constexpr (kTrB) bfr[s][j] = bq[kk][j];
-        else if constexpr (kBRows) bfr[s][j] = frag_b_rows(buf, j, kc);
         else bfr[s][j] = frag(&sBf[buf][wn + 32 * j + lr][0], wn + 32 * j + lr, kc);
       }
     };
@@ -1417,7 +1663,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     }
     // region order: the first fragment reads, then per k-step the MFMAs
     // interleaved with the next k-step's reads, then the last k-step's MFMAs
-    constexpr int kReads = kMI + (kTrB ? 0 : kNI * (kBRows ? 2 : 1));
+    constexpr int kReads = kMI + (kTrB ? 0 : kNI);
     __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
     sched_interleave<kSub - 1, kMI * kNI, kReads>();
     __builtin_amdgcn_sched_group_barrier(0x008, kMI * kNI, 0);
@@ -1425,9 +1671,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 
   // The barrier after each stage both publishes the stage just loaded (every
   // wave has waited for its own loads) and frees the buffer just read.
-  const int nk_all = K / kBK;
-  const int nk = (nk_all - kg + KG - 1) / KG;      // this group's stages
-  const int nk_max = (nk_all + KG - 1) / KG;
   // Wait until stage `s` has landed when `later` stages were requested after
   // it (and, for a prefetched first stage, this wave's stores in between).
   auto wait_stage = [&](int later, bool stores) {
@@ -1454,7 +1697,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // persistent apply: the next tile's first stage is requested at the start
   // of this tile's last stage, into the buffer no stage of this tile uses
   // then, so that it lands during that stage and the epilogue
-  const int nslot = live(slot + step);
   for (int kt = 0; kt < nk_max; ++kt) {
     const int buf = (base + kt) & (kNBuf - 1);
     // the next stage's copies go out first, into the buffer of stage kt - 1,
@@ -1485,6 +1727,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // (the barrier after the last stage means no wave reads the operand
   // buffers any more)
   if (kPersistent) base = (base + nk) & (kNBuf - 1);
+  }
   if constexpr (KG > 1) {
     // the groups' sums, in group order; only group 0 goes on to the epilogue
     // (a barrier waits only for the waves still running)
@@ -1774,22 +2017,22 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 // One entry point per Newton-Schulz product, so profiles name each stage.
 // NB: LDS stages, 0 for the usual number of the tile.
 template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_gram_kernel(GemmArgs g) {
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_gram_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kGram, BT, NB, KG>::kBytes];
   gemm_body<T, kGram, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
 template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_poly_kernel(GemmArgs g) {
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_poly_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kPoly, BT, NB, KG>::kBytes];
   gemm_body<T, kPoly, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
 template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_apply_kernel(GemmArgs g) {
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
   gemm_body<T, kApply, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
 template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG) void ns_apply_last_kernel(GemmArgs g) {
+__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_last_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
   gemm_body<T, kApply, BT, true, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
@@ -1902,19 +2145,30 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
   const int per_cu = l.tile == 256 ? 1 : (l.tile == 128 ? 2 : 4);
   const int per_xcd = (mode != kApply || l.last) ? l.max_count : (l.chip.cus / l.chip.xcds) * per_cu;
   const dim3 grid(unsigned(l.max_count < per_xcd ? l.max_count : per_xcd) * unsigned(l.chip.xcds));
-#define LM_LAUNCH(KERNEL, T, BT) \
-  hipLaunchKernelGGL((KERNEL<T, BT>), grid, dim3(TileGeom<BT>::kThreads), 0, stream, a)
-#define LM_LAUNCH_MODE(T, BT)                                   \
-  do {                                                          \
-    if (mode == kGram) LM_LAUNCH(ns_gram_kernel, T, BT);        \
-    else if (mode == kPoly) LM_LAUNCH(ns_poly_kernel, T, BT);   \
-    else if (!l.last) LM_LAUNCH(ns_apply_kernel, T, BT);        \
-    else LM_LAUNCH(ns_apply_last_kernel, T, BT);                \
+#define LM_LAUNCH_SYM(T, BT, NB, KG)                                                               \
+  do {                                                                                             \
+    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
+    if (mode == kGram) hipLaunchKernelGGL((ns_gram_kernel<T, BT, NB, KG>), full, block, 0, stream, a); \
+    else hipLaunchKernelGGL((ns_poly_kernel<T, BT, NB, KG>), full, block, 0, stream, a);           \
   } while (0)
+#define LM_LAUNCH_APPLY(T, BT, NB, KG)                                                             \
+  do {                                                                                             \
+    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
+    if (!l.last) hipLaunchKernelGGL((ns_apply_kernel<T, BT, NB, KG>), KG == 1 && sizeof(T) == 2 ? grid : full, block, 0, stream, a); \
+    else hipLaunchKernelGGL((ns_apply_last_kernel<T, BT, NB, KG>), full, block, 0, stream, a);     \
+  } while (0)
+  // one workgroup per tile, except the persistent apply
+  const dim3 full(unsigned(l.max_count) * unsigned(l.chip.xcds));
+  const int variant = l.tile * 100 + l.bufs * 10 + l.groups;
   if (l.fp32) {
-    if (l.tile == 64) LM_LAUNCH_MODE(float, 64);
-    else if (l.tile == 128) LM_LAUNCH_MODE(float, 128);
-    else return hipErrorInvalidValue;
+    if (l.tile != 64 && l.tile != 128) return hipErrorInvalidValue;
+    if (mode == kApply) {
+      if (l.tile == 64) LM_LAUNCH_APPLY(float, 64, 0, 1);
+      else LM_LAUNCH_APPLY(float, 128, 0, 1);
+    } else {
+      if (l.tile == 64) LM_LAUNCH_SYM(float, 64, 0, 1);
+      else LM_LAUNCH_SYM(float, 128, 0, 1);
+    }
   } else if (l.tile == 256) {
     if (mode == kApply && l.tail_max_count > 0) {
       // with the last round's small tiles: one workgroup per CU at a time
@@ -1940,39 +2194,24 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
       }
 #undef LM_LAUNCH_PAIR
     } else {
-      LM_LAUNCH_MODE(bf16, 256);
+      if (mode == kApply) LM_LAUNCH_APPLY(bf16, 256, 0, 1);
+      else LM_LAUNCH_SYM(bf16, 256, 0, 1);
     }
   } else {
-    // one workgroup per tile, except the persistent apply
-    const dim3 full(unsigned(l.max_count) * unsigned(l.chip.xcds));
-#define LM_LAUNCH_SYM(BT, NB, KG)                                                                  \
-  do {                                                                                             \
-    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
-    if (mode == kGram) hipLaunchKernelGGL((ns_gram_kernel<bf16, BT, NB, KG>), full, block, 0, stream, a); \
-    else hipLaunchKernelGGL((ns_poly_kernel<bf16, BT, NB, KG>), full, block, 0, stream, a);        \
-  } while (0)
-#define LM_LAUNCH_APPLY(BT, NB)                                                                    \
-  do {                                                                                             \
-    const dim3 block(TileGeom<BT>::kThreads);                                                      \
-    if (!l.last) hipLaunchKernelGGL((ns_apply_kernel<bf16, BT, NB>), grid, block, 0, stream, a);   \
-    else hipLaunchKernelGGL((ns_apply_last_kernel<bf16, BT, NB>), full, block, 0, stream, a);      \
-  } while (0)
     if (mode == kApply) {
-      if (l.tile == 128 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_APPLY(128, 2);
-      else if (l.tile == 64 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_APPLY(64, 2);
+      if (variant == 12821) LM_LAUNCH_APPLY(bf16, 128, 2, 1);
+      else if (variant == 6421) LM_LAUNCH_APPLY(bf16, 64, 2, 1);
       else return hipErrorInvalidValue;
     } else {
-      if (l.tile == 128 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_SYM(128, 2, 1);
-      else if (l.tile == 64 && l.bufs == 2 && l.groups == 1) LM_LAUNCH_SYM(64, 2, 1);
-      else if (l.tile == 64 && l.bufs == 4 && l.groups == 1) LM_LAUNCH_SYM(64, 4, 1);
-      else if (l.tile == 64 && l.bufs == 4 && l.groups == 2) LM_LAUNCH_SYM(64, 4, 2);
+      if (variant == 12821) LM_LAUNCH_SYM(bf16, 128, 2, 1);
+      else if (variant == 6421) LM_LAUNCH_SYM(bf16, 64, 2, 1);
+      else if (variant == 6441) LM_LAUNCH_SYM(bf16, 64, 4, 1);
+      else if (variant == 6442) LM_LAUNCH_SYM(bf16, 64, 4, 2);
       else return hipErrorInvalidValue;
     }
+  }
 #undef LM_LAUNCH_SYM
 #undef LM_LAUNCH_APPLY
-  }
-#undef LM_LAUNCH_MODE
-#undef LM_LAUNCH
   return hipGetLastError();
 }
 

@@ -181,8 +181,12 @@ std::vector<int64_t> stages_of(const std::vector<MuonMat>& mats, const std::vect
 // 42 -> 19, 15 -> 9, 29 -> 18; sixteen 256 x 1024 15 -> 7, 9 -> 5, 18 -> 9. At
 // two layers the apply's 256-tiles are level (31 against 34), at four all
 // three are; at twelve 64-tiles lose (Gram 86 -> 130, apply 168 -> 300).
-void pick_fine(Plan* p, int st) {
-  const std::vector<GemmTask>& macro = st == 0 ? p->gram[0] : (st == 1 ? p->poly[0] : p->apply[0]);
+//
+// fp32 (`pr` = 1): 64-tiles, one to a CU, or 128-tiles, two, whichever is
+// estimated to finish sooner; 768 x 768: 15-17 us a product in 64-tiles, 35-37 in
+// 128-tiles; the apply of two 1000 x 3000: 118 and 93.
+void pick_fine(Plan* p, int pr, int st) {
+  const std::vector<GemmTask>& macro = st == 0 ? p->gram[pr] : (st == 1 ? p->poly[pr] : p->apply[pr]);
   const size_t cus = size_t(p->chip.cus);
   if (macro.empty() || macro.size() >= 8 * cus || p->chip.cus < p->chip.xcds) return;
   struct Choice {
@@ -196,32 +200,37 @@ void pick_fine(Plan* p, int st) {
                                {{128, 2, 1, 2}, {78, 62, 250}, false}};
   static const Choice app[] = {{{64, 2, 1, 4}, {46, 19, 150}, false},
                                {{128, 2, 1, 2}, {85, 55, 300}, false}};
+  static const Choice f32[] = {{{64, 2, 1, 1}, {85, 85, 450}, false},
+                               {{128, 2, 1, 2}, {240, 265, 600}, false}};
   const StageCost big = st < 2 ? StageCost{150, 150, 500} : StageCost{200, 200, 400};
   const XcdSplit& msplit = st == 0 ? p->gram_split[0] : (st == 1 ? p->poly_split[0] : p->apply_split[0]);
   int64_t best = 0;
-  if (p->tile[0][st] == kTileBig) {
+  if (pr == 1) {
+    best = INT64_MAX / 108;                // (the usual tiles cover the padding too)
+  } else if (p->tile[0][st] == kTileBig) {
     best = launch_estimate(stages_of(p->mats, macro, st), msplit, 1, big, p->chip);
     // the apply's first start and last store, and the last round's small tiles
     if (st == 2) best += p->apply_tail[0].empty() ? 300 : 600;
   } else {
     best = launch_estimate(stages_of(p->mats, macro, st), msplit, 2, sym[3].c, p->chip);
   }
-  for (const Choice* k = st < 2 ? sym : app; k != (st < 2 ? sym + 4 : app + 2); ++k) {
+  const Choice* first = pr == 1 ? f32 : (st < 2 ? sym : app);
+  for (const Choice* k = first; k != first + (first == sym ? 4 : 2); ++k) {
     const GemmVariant v = k->v;
     const StageCost c = k->c;
     std::vector<GemmTask> tasks;
     std::vector<int64_t> cost;
-    fine_tiles(p->mats, 0, st, v.tile, &tasks, &cost);
+    fine_tiles(p->mats, pr, st, v.tile, &tasks, &cost);
     if (k->one_round && tasks.size() > cus) continue;
     XcdSplit split;
     split_by_xcd(&tasks, cost, p->chip.xcds, &split);
     const int64_t est = launch_estimate(stages_of(p->mats, tasks, st), split, v.slots, c, p->chip);
     // 8% less, or the tiles stay as they are: about the spread between boxes
-    if (est * 108 >= best * 100) continue;
+    if (est * (pr == 1 ? 100 : 108) >= best * 100) continue;
     best = est;
-    p->variant[0][st] = v;
-    p->fine[0][st].swap(tasks);
-    p->fine_split[0][st] = split;
+    p->variant[pr][st] = v;
+    p->fine[pr][st].swap(tasks);
+    p->fine_split[pr][st] = split;
   }
 }
 
@@ -562,7 +571,8 @@ Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
     split_by_xcd(&p->apply[pr], ca, chip.xcds, &p->apply_split[pr]);
     split_by_xcd(&p->apply_tail[pr], ct, chip.xcds, &p->apply_tail_split[pr]);
   }
-  for (int st = 0; st < 3; ++st) pick_fine(p, st);
+  for (int pr = 0; pr < 2; ++pr)
+    for (int st = 0; st < 3; ++st) pick_fine(p, pr, st);
 
   size_t off = align256(size_t(ns_off));
   p->ws_partials_off = off;

@@ -62,3 +62,35 @@ def test_small_tiles_match_oracle(name):
     for i in range(len(shapes)):
         check_muon(W0[i], G[i], M0[i], W[i].cpu().double().numpy(), M[i].cpu().double().numpy(),
                    0.9, 0.99, 0.02, 0.1, "bf16")
+
+
+# fp32 products: K loops of 1 to 9 stages of 64 on 64-tiles (a round is 8), tile edges,
+# and (the pair of 1000 x 1500) 128-tiles with an odd number of stages of 32
+F32_LISTS = {
+    "one-stage": [(2, 3), (33, 64), (64, 40)],
+    "edges": [(65, 129), (129, 193), (257, 191), (63, 449)],
+    "rounds": [(512, 513), (577, 513), (100, 1089)],
+    "tile-128": [(1000, 1510), (1510, 1000), (980, 1510)],
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(F32_LISTS))
+def test_split_fp32_products_match_oracle(name):
+    import torch
+
+    from paper_2605_19811_amd import lionmuon as lm
+    from parity import check_muon
+    shapes = F32_LISTS[name]
+    rng = np.random.default_rng(len(shapes) + shapes[0][0])
+    W0, M0, G = ([(rng.standard_normal(s) * std).astype(np.float32) for s in shapes]
+                 for std in (0.02, 1e-2, 1e-2))
+    W, M, Gd = ([torch.from_numpy(x).cuda() for x in t] for t in (W0, M0, G))
+    cfg = lm.config(ns_precision="fp32", lr_muon=0.02)
+    ws = torch.full((lm.lionmuon_workspace_bytes([(*s, False) for s in shapes], cfg),), 0xFF,
+                    dtype=torch.uint8, device="cuda")
+    lm.lionmuon_step_ex(W, Gd, M, 0, 1, 0.9, 0.99, 0.1, cfg, workspace=ws)
+    torch.cuda.synchronize()
+    for i in range(len(shapes)):
+        check_muon(W0[i], G[i], M0[i], W[i].cpu().double().numpy(), M[i].cpu().double().numpy(),
+                   0.9, 0.99, 0.02, 0.1, "fp32")
