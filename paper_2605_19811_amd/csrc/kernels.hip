@@ -211,10 +211,18 @@ constexpr int kPrepLdsBytes = 64 * 66 * 4;
 // of rows (1 KB of fp32 for TC = 256). G and M are read and M written with
 // the non-temporal hint (the step does not touch them again); X is stored
 // normally, since the first Gram product reads it next.
-template <typename T, int TC>
+//
+// VEC: the rows of G, M are 16-byte aligned and a lane takes four consecutive
+// columns, all inside the matrix or all outside. Otherwise consecutive lanes
+// take consecutive columns, so that a wave still reads and writes whole lines
+// (two 595-wide layers 39 -> 30 us; with four consecutive elements a lane, each
+// access touched four times the lines), with ordinary loads and stores: the lines at
+// the ends of a row piece are used twice.
+template <typename T, int TC, bool VEC>
 __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, int b) {
   constexpr int kChunks = TC / 4, kRowsPass = 256 / kChunks, kRows = kPrepElems / TC;
   constexpr int kPasses = kRows / kRowsPass;
+  constexpr int kStep = VEC ? 1 : kChunks;       // columns between a lane's four elements
   static_assert(kPasses * kRowsPass == kRows, "whole passes per strip");
   __shared__ float red[4];
   const float* G = a.bind[mm.tensor].g;
@@ -223,7 +231,7 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
   const int ti = local / mm.prep_tiles_n, tj = local - ti * mm.prep_tiles_n;
   T* X = reinterpret_cast<T*>(static_cast<char*>(a.ws) + mm.off_x[0]);
   const int64_t cols_pad = mm.l_pad;
-  const int tid = threadIdx.x, r0 = tid / kChunks, c4 = (tid % kChunks) * 4;
+  const int tid = threadIdx.x, r0 = tid / kChunks, c4 = (tid % kChunks) * (VEC ? 4 : 1);
   float ss = 0.0f;
 #pragma unroll
   for (int u = 0; u < kPasses; ++u) {
@@ -231,7 +239,7 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
     const int64_t q = int64_t(tj) * TC + c4;
     float gv[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {0.f, 0.f, 0.f, 0.f};
     const bool row_in = p < mm.rows;
-    const bool vec = row_in && mm.vec_ok && q + 3 < mm.cols;
+    const bool vec = VEC && row_in && q < mm.cols;
     const int64_t idx = p * mm.cols + q;
     if (vec) {
       const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(G + idx));
@@ -240,13 +248,15 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
         const f32x4 m = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Mp + idx));
         mv[0] = m[0]; mv[1] = m[1]; mv[2] = m[2]; mv[3] = m[3];
       }
-    } else if (row_in) {
+    } else if constexpr (!VEC) {
+      // (clamped addresses: a branch an element would serialise the loads)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (q + e < mm.cols) {
-          gv[e] = G[idx + e];
-          if (Mp) mv[e] = Mp[idx + e];
-        }
+        const bool in = row_in && q + kStep * e < mm.cols;
+        const int64_t i = in ? idx + kStep * e : 0;
+        const float g = G[i], m = Mp ? Mp[i] : 0.0f;
+        gv[e] = in ? g : 0.0f;
+        mv[e] = in ? m : 0.0f;
       }
     }
     float c[4], mn[4];
@@ -260,13 +270,18 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
       if (vec) {
         const f32x4 mv4 = {mn[0], mn[1], mn[2], mn[3]};
         __builtin_nontemporal_store(mv4, reinterpret_cast<f32x4*>(Mp + idx));
-      } else if (row_in) {
+      } else if (!VEC && row_in) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (q + e < mm.cols) Mp[idx + e] = mn[e];
+          if (q + kStep * e < mm.cols) Mp[idx + kStep * e] = mn[e];
       }
     }
-    store4(X + p * cols_pad + q, c);
+    if constexpr (VEC) {
+      store4(X + p * cols_pad + q, c);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) X[p * cols_pad + q + kStep * e] = to_elem<T>(c[e]);
+    }
   }
   ss = wave_sum(ss);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
@@ -278,12 +293,13 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
 // pieces), stored transposed (X = Ghat^T) through LDS as 64-element pieces of
 // TC rows of X. TC = kPrepTallCols (bf16 X) or kPrepTile (fp32 X), so both
 // tiles fit the same LDS block.
-template <typename T, int TC>
+template <typename T, int TC, bool VEC>
 __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, int b,
                                           char* lds) {
   constexpr int kTR = kPrepTile, kTC = TC;
   constexpr int kPad = 4 / sizeof(T) + 1;        // odd word stride per LDS row
   constexpr int kChunks = kTC / 4, kRowsPass = 256 / kChunks, kPasses = kTR / kRowsPass;
+  constexpr int kStep = VEC ? 1 : kChunks;       // columns between a lane's four elements
   static_assert(kTR * (kTC + kPad) * sizeof(T) <= kPrepLdsBytes, "tile fits the LDS block");
   T (*tile)[kTC + kPad] = reinterpret_cast<T (*)[kTC + kPad]>(lds);
   __shared__ float red[4];
@@ -293,7 +309,7 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
   const int ti = local / mm.prep_tiles_n, tj = local - ti * mm.prep_tiles_n;
   const int64_t rows_pad = mm.l_pad;           // of the original (tall) matrix
   T* X = reinterpret_cast<T*>(static_cast<char*>(a.ws) + mm.off_x[0]);
-  const int tid = threadIdx.x, r0 = tid / kChunks, c4 = (tid % kChunks) * 4;
+  const int tid = threadIdx.x, r0 = tid / kChunks, c4 = (tid % kChunks) * (VEC ? 4 : 1);
   float ss = 0.0f;
 #pragma unroll
   for (int u = 0; u < kPasses; ++u) {
@@ -302,7 +318,7 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
     const int64_t q = int64_t(tj) * kTC + c4;
     float gv[4] = {0.f, 0.f, 0.f, 0.f}, mv[4] = {0.f, 0.f, 0.f, 0.f};
     const bool row_in = p < mm.rows;
-    const bool vec = row_in && mm.vec_ok && q + 3 < mm.cols;
+    const bool vec = VEC && row_in && q < mm.cols;
     const int64_t idx = p * mm.cols + q;
     if (vec) {
       const f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(G + idx));
@@ -311,13 +327,15 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
         const f32x4 m = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(Mp + idx));
         mv[0] = m[0]; mv[1] = m[1]; mv[2] = m[2]; mv[3] = m[3];
       }
-    } else if (row_in) {
+    } else if constexpr (!VEC) {
+      // (clamped addresses: a branch an element would serialise the loads)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (q + e < mm.cols) {
-          gv[e] = G[idx + e];
-          if (Mp) mv[e] = Mp[idx + e];
-        }
+        const bool in = row_in && q + kStep * e < mm.cols;
+        const int64_t i = in ? idx + kStep * e : 0;
+        const float g = G[i], m = Mp ? Mp[i] : 0.0f;
+        gv[e] = in ? g : 0.0f;
+        mv[e] = in ? m : 0.0f;
       }
     }
     float c[4], mn[4];
@@ -331,14 +349,14 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
       if (vec) {
         const f32x4 mv4 = {mn[0], mn[1], mn[2], mn[3]};
         __builtin_nontemporal_store(mv4, reinterpret_cast<f32x4*>(Mp + idx));
-      } else if (row_in) {
+      } else if (!VEC && row_in) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (q + e < mm.cols) Mp[idx + e] = mn[e];
+          if (q + kStep * e < mm.cols) Mp[idx + kStep * e] = mn[e];
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) tile[r][c4 + e] = to_elem<T>(c[e]);
+    for (int e = 0; e < 4; ++e) tile[r][c4 + kStep * e] = to_elem<T>(c[e]);
   }
   __syncthreads();
   // X^T rows: kTC of them, kTR elements each, 4 per thread
@@ -358,22 +376,28 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
   if (tid == 0) a.partials[mm.prep_first + local] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+template <bool VEC>
+__device__ __forceinline__ void prep_tile(const PrepArgs& a, const MuonMat& mm, int b, char* lds) {
+  if (mm.transposed) {
+    if (mm.fp32) prep_tall<float, kPrepTile, VEC>(a, mm, b, lds);
+    else prep_tall<bf16, kPrepTallCols, VEC>(a, mm, b, lds);
+  } else if (mm.l_pad == mm.prep_tiles_n * 256) {
+    if (mm.fp32) prep_wide<float, 256, VEC>(a, mm, b);
+    else prep_wide<bf16, 256, VEC>(a, mm, b);
+  } else {
+    if (mm.fp32) prep_wide<float, 128, VEC>(a, mm, b);
+    else prep_wide<bf16, 128, VEC>(a, mm, b);
+  }
+}
+
 __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
   __shared__ __attribute__((aligned(16))) char lds[kPrepLdsBytes];
   const int b = blockIdx.x;
   const int mi = find_segment(a.prep_start, a.n_mats, b);
   if (a.decide && a.decide[mi] == 0) return;          // the candidate took Lion
   const MuonMat& mm = a.mats[mi];
-  if (mm.transposed) {
-    if (mm.fp32) prep_tall<float, kPrepTile>(a, mm, b, lds);
-    else prep_tall<bf16, kPrepTallCols>(a, mm, b, lds);
-  } else if (mm.l_pad == mm.prep_tiles_n * 256) {
-    if (mm.fp32) prep_wide<float, 256>(a, mm, b);
-    else prep_wide<bf16, 256>(a, mm, b);
-  } else {
-    if (mm.fp32) prep_wide<float, 128>(a, mm, b);
-    else prep_wide<bf16, 128>(a, mm, b);
-  }
+  if (mm.vec_ok) prep_tile<true>(a, mm, b, lds);
+  else prep_tile<false>(a, mm, b, lds);
 }
 
 __global__ __launch_bounds__(256) void norm_kernel(PrepArgs a) {
@@ -1940,20 +1964,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
       const int64_t wrow0 = tall ? col0 : row0, wcol0 = tall ? row0 : col0;
       const int64_t wrows = mm.rows, wcols = mm.cols;
       const float kappa = mm.kappa;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        f32x4 wv[kIter];
-        if (!g.store_o) {
-#pragma unroll
-          for (int it = 0; it < kIter; ++it) {
-            const int idx = tid + it * kNT;
-            const int i = idx / (BT / 4), j = (idx % (BT / 4)) * 4;
-            const int64_t gr = wrow0 + h * kHalf + i, gc = wcol0 + j;
-            wv[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (mm.vec_ok && gr < wrows && gc + 3 < wcols)
-              wv[it] = *reinterpret_cast<const f32x4*>(Wp + gr * wcols + gc);
-          }
-        }
+      auto stage_half = [&](int h) {
 #pragma unroll
         for (int mi = 0; mi < kMI; ++mi)
 #pragma unroll
@@ -1973,6 +1984,61 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
                 store4(&fst[c - h * kHalf][r], o);
               }
             }
+      };
+      // Rows of W that are not 16-byte aligned, on the tiles short lists take:
+      // consecutive lanes take consecutive elements of a row and request them
+      // before O is staged (two 595-wide layers 47 -> 38 us; 128- and 256-tiles, whose
+      // other update this made slower, take the general path below)
+      bool rows_done = false;
+      if constexpr (BT == 64 || sizeof(T) == 4) {
+        if (!mm.vec_ok) {
+          rows_done = true;
+          constexpr int kElems = kHalf * BT / kNT;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            float wv[kElems];
+            auto place = [&](int it, int64_t& gr, int64_t& gc) {
+              const int idx = tid + it * kNT;
+              gr = wrow0 + h * kHalf + idx / BT;
+              gc = wcol0 + idx % BT;
+              return gr < wrows && gc < wcols;
+            };
+#pragma unroll
+            for (int it = 0; it < kElems; ++it) {
+              int64_t gr, gc;
+              const bool in = place(it, gr, gc);
+              wv[it] = g.store_o ? 0.0f : Wp[in ? gr * wcols + gc : 0];   // (clamped: no branch an element)
+            }
+            stage_half(h);
+            lds_barrier();
+#pragma unroll
+            for (int it = 0; it < kElems; ++it) {
+              int64_t gr, gc;
+              if (!place(it, gr, gc)) continue;
+              const int idx = tid + it * kNT;
+              const float o = fst[idx / BT][idx % BT], w = wv[it];
+              Wp[gr * wcols + gc] = g.store_o ? o : fmaf(-g.lr, fmaf(g.wd, w, o), w);
+            }
+            lds_barrier();
+          }
+        }
+      }
+      if (!rows_done)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        f32x4 wv[kIter];
+        if (!g.store_o) {
+#pragma unroll
+          for (int it = 0; it < kIter; ++it) {
+            const int idx = tid + it * kNT;
+            const int i = idx / (BT / 4), j = (idx % (BT / 4)) * 4;
+            const int64_t gr = wrow0 + h * kHalf + i, gc = wcol0 + j;
+            wv[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (mm.vec_ok && gr < wrows && gc + 3 < wcols)
+              wv[it] = *reinterpret_cast<const f32x4*>(Wp + gr * wcols + gc);
+          }
+        }
+        stage_half(h);
         lds_barrier();
 #pragma unroll
         for (int it = 0; it < kIter; ++it) {

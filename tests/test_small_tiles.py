@@ -94,3 +94,34 @@ def test_split_fp32_products_match_oracle(name):
     for i in range(len(shapes)):
         check_muon(W0[i], G[i], M0[i], W[i].cpu().double().numpy(), M[i].cpu().double().numpy(),
                    0.9, 0.99, 0.02, 0.1, "fp32")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec,tol", [("bf16", 2e-2), ("fp32", 1e-4)])
+@pytest.mark.parametrize("shape", [(65, 131), (131, 65), (200, 333), (333, 200)])
+def test_rows_off_16_bytes(shape, prec, tol):
+    """Rows that no 16-byte access divides: the hook's store and a step on
+    buffers one float off (tolerances: the two precisions' error budgets)."""
+    import torch
+
+    import oracle
+    from paper_2605_19811_amd import lionmuon as lm
+    from parity import check_muon
+    rng = np.random.default_rng(shape[0])
+    W0, M0, G = ((rng.standard_normal(shape) * std).astype(np.float32) for std in (0.02, 1e-2, 1e-2))
+    cfg = lm.config(ns_precision=prec, lr_muon=0.02)
+    o = lm.lionmuon_ns(torch.from_numpy(G).cuda(), cfg).cpu().double().numpy()
+    ref = oracle.newton_schulz(G)
+    assert np.linalg.norm(o - ref) <= tol * np.linalg.norm(ref)
+
+    def off(x):
+        flat = torch.full((x.size + 2,), float("nan"), device="cuda")
+        flat[1:-1] = torch.from_numpy(x.ravel()).cuda()
+        return flat, flat[1:-1].view(*shape)
+    (fw, W), (_, Gd), (fm, M) = off(W0), off(G), off(M0)
+    lm.lionmuon_step_ex([W], [Gd], [M], 0, 1, 0.9, 0.99, 0.1, cfg)
+    torch.cuda.synchronize()
+    for flat in (fw, fm):                       # nothing written past either end
+        assert torch.isnan(flat[0]) and torch.isnan(flat[-1])
+    check_muon(W0, G, M0, W.cpu().double().numpy(), M.cpu().double().numpy(),
+               0.9, 0.99, 0.02, 0.1, prec)
