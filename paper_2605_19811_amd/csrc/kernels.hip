@@ -1285,11 +1285,17 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
   // copies of stage `ahead` behind it: in one place they stalled the wave
   // until the memory pipeline had taken them.
   auto step = [&](int slot, int kt1, int kk1, int ahead, auto fresh) {
+    // (128-tiles read a fragment one part ahead: with all four in registers two
+    // workgroups to a CU did not fit without spills)
 #pragma unroll
-    for (int f = 0; f < 4; ++f) read(f, kt1, kk1);
+    for (int f = 0; f < (BT == 128 ? 1 : 4); ++f) read(f, kt1, kk1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+      if (BT == 128 && r < 3) {
+        read(r + 1, kt1, kk1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int m = 6 * r; m < 6 * r + 6; ++m) {
         const int t = m >> 2, i = (m >> 1) & 1, j = m & 1;
