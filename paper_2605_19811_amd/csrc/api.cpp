@@ -629,7 +629,6 @@ lm_status enqueue(const DevicePlan& dp, const lm::StepConsts& k, const lm_config
         gl.fp32 = pr;
         gl.tile = fine ? v.tile : p.tile[pr][st3];
         gl.bufs = v.bufs;
-        gl.groups = v.groups;
         // the apply's last round as smaller tiles, in the same launch
         const bool tail = !fine && st3 == 2 && p.apply_tail_split[pr].max_count > 0;
         gl.tail_tasks = tail ? dp.d_tasks[pr][3] : nullptr;

@@ -65,8 +65,7 @@ struct GemmLaunch {
   float lr, wd;                  // eta_M and lambda of the W update
   int32_t fp32;                  // element type of the matrices in `tasks`
   int32_t tile;                  // output tile edge of `tasks`: 64, 128 or 256
-  int32_t bufs = 2;              // LDS stages, and groups of waves that share a
-  int32_t groups = 1;            // tile's K loop (bf16 64- and 128-tiles)
+  int32_t bufs = 2;              // LDS stages (bf16 64- and 128-tiles)
   const int32_t* decide;         // adaptive: tiles of matrices with decision 0 exit
   // apply on bf16 256-tiles only: the last round's smaller tiles (64 or 128),
   // run by extra workgroups of the same launch; none when tail_max_count is 0

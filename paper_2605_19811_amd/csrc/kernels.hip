@@ -952,9 +952,11 @@ __global__ __launch_bounds__(256) void srank_decide_kernel(SrankArgs a) {
 //             round when sixteen times its leftover 256-tiles fit one round).
 // A small tile alone on its CU is bound by latency: 0.27 us a K stage of a
 // 64-tile with four LDS stages, 0.46 with two, 0.78 of a 128-tile with two.
-// So short lists take four stages, or (one tile per CU at most) four stages
-// in each of KG = 2 groups of waves that share the K loop (0.20 us a stage);
-// longer ones two stages, and four workgroups to a CU.
+// So short lists take four stages, or (one tile per CU at most) eight with waves
+// that only copy (ring_product, 0.17 us a stage); longer ones two stages, and
+// four workgroups to a CU. In all of them an element's sum runs through K in
+// order: a bf16 matrix has the same result, to the bit, in every list (two groups
+// of waves that shared a K loop, 0.20 us a stage, moved results by 2.5e-3).
 // Accumulator element r of block (mi, ni) sits at row
 // wm + 32 mi + 8 (r / 4) + 4 (lane / 32) + r % 4, col wn + 32 ni + lane % 32.
 // Wait until at most N vector-memory operations of this wave are outstanding
@@ -1142,7 +1144,7 @@ struct GemmArgs {
 
 // LDS of one product tile: kNBuf operand stages during the K loop, then the
 // output tile (the kernel declares it; the tile body takes a pointer).
-template <typename T, int MODE, int BT, int NB = 0, int KG = 1>
+template <typename T, int MODE, int BT, int NB = 0>
 struct GemmLds {
   static constexpr int kLd = Mfma<T>::kBK;      // LDS row: 128 bytes
   static constexpr int kStR = BT + 16;          // row-major staging row stride
@@ -1153,7 +1155,7 @@ struct GemmLds {
   // NB > 0 sets the count (64-tiles of lists that leave CUs idle).
   static constexpr int kNBuf = NB > 0 ? NB : (sizeof(T) == 2 && (BT == 64 || (MODE == kApply && BT == 128))) ? 4 : 2;
   // fp32: four stages (128-tiles: two) of 16 KB an operand (split_product)
-  static constexpr int kOperand = sizeof(T) == 4 ? (BT == 128 ? 2 : 4) * 2 * 128 * 32 : kNBuf * KG * 2 * BT * kLd, kStage = BT * kStR;
+  static constexpr int kOperand = sizeof(T) == 4 ? (BT == 128 ? 2 : 4) * 2 * 128 * 32 : kNBuf * 2 * BT * kLd, kStage = BT * kStR;
   static constexpr int kElems = kOperand > kStage ? kOperand : kStage;
   static constexpr int kBytes = kElems * int(sizeof(T));
 };
@@ -1385,12 +1387,90 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
   }
 }
 
+// K loop of one bf16 64-tile of a symmetric product that has its CU to itself:
+// four waves multiply (a 32 x 32 block each) and four more (`copier`) do nothing
+// but request the operands, seven stages of 64 K values ahead, so that no wave
+// that multiplies waits for the memory pipeline to take a copy. The fragments
+// of a stage are read while the stage before is multiplied: in one piece a
+// stage was LDS latency, then four dependent MFMAs, then a barrier. What bounds
+// it is the LDS, 32 KB of fragment reads and 16 KB of copies a stage. Per stage
+// of a 768 x 3072 Gram: 0.17 us (the launch 11-12 us); 0.27 by four waves that copy and multiply, four or eight
+// stages deep, 0.34 with two stages to a barrier, 0.24 by copiers alone. An
+// element's sum runs through K in order, as in every other bf16 tile.
+__device__ __forceinline__ void ring_product(const GemmOps<bf16>& o, bf16* smem, int tid, bool copier, f32x16& acc) {
+  using M = Mfma<bf16>;
+  constexpr int kNBuf = 8, kBK = M::kBK, kSub = kBK / M::kKStep, kOperand = 64 * kBK, kOps = 4;
+  const int lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nk = o.K / kBK;
+  auto buf = [&](int kt) { return smem + (kt & (kNBuf - 1)) * 2 * kOperand; };
+  if (copier) {
+    auto copy = [&](int kt) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        bf16* dst = buf(kt) + (q * 4 + wave) * 8 * kBK;
+        copy16(o.a + int64_t(q * 32) * o.lda + kt * kBK, o.a_off, dst);
+        copy16(o.b + int64_t(q * 32) * o.ldb + kt * kBK, o.b_off, dst + kOperand);
+      }
+    };
+#pragma unroll
+    for (int st = 0; st < kNBuf - 1; ++st)
+      if (st < nk) copy(st);
+    wait_stages<kNBuf - 2, kOps, 0>(min(nk - 1, kNBuf - 2));   // stage 0
+    lds_barrier();
+    for (int kt = 0; kt < nk; ++kt) {
+      // stage kt + 1 (stages up to kt + 6 have been requested)
+      wait_stages<kNBuf - 3, kOps, 0>(max(0, min(nk - 2 - kt, kNBuf - 3)));
+      lds_barrier();
+      // into the buffer of stage kt - 1, which every wave had multiplied
+      // before this barrier
+      if (kt + kNBuf - 1 < nk) copy(kt + kNBuf - 1);
+    }
+    lds_barrier();
+    return;
+  }
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  M::Frag fa[2][kSub], fb[2][kSub];              // [parity of the stage][K step]
+  auto read = [&](int par, int kt) {
+    const bf16* a = buf(kt) + (wm + lr) * kBK;
+    const bf16* b = buf(kt) + kOperand + (wn + lr) * kBK;
+    const int swz = (lr & 7) ^ ((lr >> 3) & 1);  // (of the row: wm and wn are multiples of 16)
+#pragma unroll
+    for (int kk = 0; kk < kSub; ++kk) {
+      const int off = ((kk * 2 + lk) ^ swz) * 8;
+      fa[par][kk] = M::load(a + off, 0);
+      fb[par][kk] = M::load(b + off, 0);
+    }
+  };
+  auto stage = [&](int par, int kt) {
+    // (no wait for the reads in flight: the stage they read is not
+    // overwritten before it has been multiplied)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(par ^ 1, min(kt + 1, nk - 1));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < kSub; ++kk) acc = M::mma(fa[par][kk], fb[par][kk], acc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  lds_barrier();
+  read(0, 0);
+  int kt = 0;
+  for (; kt + 2 <= nk; kt += 2) {
+    stage(0, kt);
+    stage(1, kt + 1);
+  }
+  if (kt < nk) stage(0, kt);
+  lds_barrier();
+}
+
 // LAST (apply only): the last Newton-Schulz step, whose epilogue updates W
 // (its own instantiation: that epilogue's registers would otherwise weigh
 // on every other apply step). `smem` is the kernel's LDS block (at least
 // GemmLds<T, MODE, BT>::kBytes); the workgroup is number `bid` of the `nblk`
 // that run this task list (workgroup i on XCD i mod xcds).
-template <typename T, int MODE, int BT, bool LAST = false, int NB = 0, int KG = 1>
+template <typename T, int MODE, int BT, bool LAST = false, int NB = 0>
 __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, int nblk) {
   using M = Mfma<T>;
   using Geo = TileGeom<BT>;
@@ -1403,19 +1483,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // rows, 8 or 16 dwords apart modulo the 64 banks, so a quad of lanes
   // writing 4 consecutive rows never collides), kStC for transposed staging
   // (4 dwords apart, so 16 lanes writing 16 consecutive rows never collide).
-  using L = GemmLds<T, MODE, BT, NB, KG>;
+  using L = GemmLds<T, MODE, BT, NB>;
   constexpr int kStR = L::kStR, kStC = BT + kEpc;
   constexpr int kNBuf = L::kNBuf;
-  // K groups: the waves of group kg take every KG-th K stage, into buffers of
-  // their own; their sums meet in LDS after the K loop.
-  const int kg = KG == 1 ? 0 : int(__builtin_amdgcn_readfirstlane(threadIdx.x / kNT));
-  T* smem_g = smem + kg * (L::kOperand / KG);
-  T (*sA)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g);
-  T (*sB)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem_g + kNBuf * BT * kLd);
+  // 64-tiles with eight stages: the second half of the workgroup copies
+  constexpr bool kRing = NB == 8;
+  static_assert(!kRing || (MODE != kApply && BT == 64 && sizeof(T) == 2), "ring_product's tile");
+  const bool copier = kRing && int(__builtin_amdgcn_readfirstlane(threadIdx.x)) >= kNT;
+  T (*sA)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem);
+  T (*sB)[BT][kLd] = reinterpret_cast<T (*)[BT][kLd]>(smem + kNBuf * BT * kLd);
   // apply: the B operand (X, K = s along its rows) is staged k-major as
   // kBK rows of BT elements (512 bytes) and read transposed
   constexpr bool kBRows = MODE == kApply;
-  T (*sBr)[kBK][BT] = reinterpret_cast<T (*)[kBK][BT]>(smem_g + kNBuf * BT * kLd);
+  T (*sBr)[kBK][BT] = reinterpret_cast<T (*)[kBK][BT]>(smem + kNBuf * BT * kLd);
 
   // The workgroups of an XCD walk that XCD's tile list with a stride of
   // their number, skipping the tiles of matrices whose adaptive decision
@@ -1424,7 +1504,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // registers, so the next tile's loads overlap them. The other products
   // stage their results through the whole LDS and run one tile per
   // workgroup, so a finished workgroup's successor starts at once.
-  constexpr bool kPersistent = MODE == kApply && !LAST && KG == 1 && sizeof(T) == 2;
+  constexpr bool kPersistent = MODE == kApply && !LAST && sizeof(T) == 2;
   const int xcds = g.xcds;
   const int xcd = bid % xcds;
   const int count = kconst(g.split)->count[xcd];
@@ -1447,7 +1527,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // Lane-derived values are recomputed for every tile (the empty asm keeps
   // the compiler from hoisting them out of the tile loop, where they would
   // stay live, in registers, through the epilogue).
-  int tid = KG == 1 ? int(threadIdx.x) : int(threadIdx.x) - kg * kNT;
+  int tid = kRing ? int(threadIdx.x) % kNT : int(threadIdx.x);
   if constexpr (kPersistent) asm volatile("" : "+v"(tid));
   __builtin_assume(tid >= 0 && tid < kNT);
 
@@ -1558,12 +1638,13 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  const int nk_all = K / kBK;
-  const int nk = (nk_all - kg + KG - 1) / KG;      // this group's stages
-  const int nk_max = (nk_all + KG - 1) / KG;
+  const int nk = K / kBK;
   const int nslot = live(slot + step);
   if constexpr (sizeof(T) == 4) {
     split_product<MODE, BT>(ops, smem, tid, acc);
+  } else if constexpr (kRing) {
+    ring_product(ops, smem, tid, copier, acc[0][0]);
+    if (copier) return;                          // (a barrier waits only for the waves still running)
   } else {
   auto frag = [&](const T* rowp, int row, int kc) {
     const int e = kc + lk * (M::kKStep / 2);
@@ -1721,17 +1802,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   };
   // stages 0 .. kNBuf - 2 in flight before the first MFMA (stage 0 may have
   // been requested already, during the previous tile's last K stage)
-  if (!prefetched && (KG == 1 || nk > 0)) dma(ops, base, kg * kBK);
+  if (!prefetched) dma(ops, base, 0);
 #pragma unroll
   for (int st = 1; st < kNBuf - 1; ++st)
-    if (st < nk) dma(ops, (base + st) & (kNBuf - 1), (st * KG + kg) * kBK);
-  wait_stage(nk > 0 ? nk - 1 : 0, prefetched);
+    if (st < nk) dma(ops, (base + st) & (kNBuf - 1), st * kBK);
+  wait_stage(nk - 1, prefetched);
   prefetched = false;
   lds_barrier();
   // persistent apply: the next tile's first stage is requested at the start
   // of this tile's last stage, into the buffer no stage of this tile uses
   // then, so that it lands during that stage and the epilogue
-  for (int kt = 0; kt < nk_max; ++kt) {
+  for (int kt = 0; kt < nk; ++kt) {
     const int buf = (base + kt) & (kNBuf - 1);
     // the next stage's copies go out first, into the buffer of stage kt - 1,
     // which every wave finished before the barrier that ended the previous
@@ -1739,19 +1820,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
     // then overlaps this stage's transpose reads (an assembly block: the
     // compiler adds no wait for the copies before it)
     const int nxt = kt + kNBuf - 1;
-    if (nxt < nk) dma(ops, (base + nxt) & (kNBuf - 1), (nxt * KG + kg) * kBK);
+    if (nxt < nk) dma(ops, (base + nxt) & (kNBuf - 1), nxt * kBK);
     if (kPersistent && kt == nk - 1 && nslot < count) {
       dma(make_ops(tasks[nslot]), (base + nk) & (kNBuf - 1), 0);
       prefetched = true;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (KG == 1 || kt < nk) {
-      if constexpr (kTrB) {
-        preload_b(buf);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      compute(buf);
+    if constexpr (kTrB) {
+      preload_b(buf);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    compute(buf);
     __builtin_amdgcn_sched_barrier(0);
     // stage kt + 1 (after the last stage nothing: the next tile's first
     // stage stays in flight)
@@ -1761,39 +1840,6 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   // (the barrier after the last stage means no wave reads the operand
   // buffers any more)
   if (kPersistent) base = (base + nk) & (kNBuf - 1);
-  }
-  if constexpr (KG > 1) {
-    // the groups' sums, in group order; only group 0 goes on to the epilogue
-    // (a barrier waits only for the waves still running)
-    static_assert((KG - 1) * BT * BT * 4 <= L::kBytes, "sums fit the operand buffers");
-    f32x4* sums = reinterpret_cast<f32x4*>(smem);
-    auto at_sum = [&](int g2, int i, int j, int q) {
-      return sums + ((((g2 - 1) * kMI + i) * kNI + j) * 4 + q) * kNT + tid;
-    };
-    if (kg > 0) {
-#pragma unroll
-      for (int i = 0; i < kMI; ++i)
-#pragma unroll
-        for (int j = 0; j < kNI; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            *at_sum(kg, i, j, q) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-    }
-    lds_barrier();
-    if (kg > 0) return;
-#pragma unroll
-    for (int g2 = 1; g2 < KG; ++g2)
-#pragma unroll
-      for (int i = 0; i < kMI; ++i)
-#pragma unroll
-        for (int j = 0; j < kNI; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v = *at_sum(g2, i, j, q);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-          }
-    lds_barrier();
   }
 
   // ---- epilogues ----------------------------------------------------------
@@ -2090,27 +2136,30 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, T* smem, int bid, i
   }
 }
 
+// Threads of a workgroup: with eight LDS stages as many again that only copy.
+template <int BT, int NB> constexpr int block_threads() { return TileGeom<BT>::kThreads * (NB == 8 ? 2 : 1); }
+
 // One entry point per Newton-Schulz product, so profiles name each stage.
 // NB: LDS stages, 0 for the usual number of the tile.
-template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_gram_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kGram, BT, NB, KG>::kBytes];
-  gemm_body<T, kGram, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0>
+__global__ __launch_bounds__((block_threads<BT, NB>()), sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_gram_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kGram, BT, NB>::kBytes];
+  gemm_body<T, kGram, BT, false, NB>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_poly_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kPoly, BT, NB, KG>::kBytes];
-  gemm_body<T, kPoly, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0>
+__global__ __launch_bounds__((block_threads<BT, NB>()), sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_poly_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kPoly, BT, NB>::kBytes];
+  gemm_body<T, kPoly, BT, false, NB>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
-  gemm_body<T, kApply, BT, false, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0>
+__global__ __launch_bounds__((block_threads<BT, NB>()), sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB>::kBytes];
+  gemm_body<T, kApply, BT, false, NB>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
-template <typename T, int BT, int NB = 0, int KG = 1>
-__global__ __launch_bounds__(TileGeom<BT>::kThreads * KG, sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_last_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB, KG>::kBytes];
-  gemm_body<T, kApply, BT, true, NB, KG>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
+template <typename T, int BT, int NB = 0>
+__global__ __launch_bounds__((block_threads<BT, NB>()), sizeof(T) == 4 && BT == 128 ? 2 : 1) void ns_apply_last_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) char lds[GemmLds<T, kApply, BT, NB>::kBytes];
+  gemm_body<T, kApply, BT, true, NB>(g, reinterpret_cast<T*>(lds), int(blockIdx.x), int(gridDim.x));
 }
 // An apply step's 256-tiles and the small tiles of its last round in one
 // launch: the first `main_grid` workgroups run the 256-tiles, the rest the
@@ -2221,29 +2270,29 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
   const int per_cu = l.tile == 256 ? 1 : (l.tile == 128 ? 2 : 4);
   const int per_xcd = (mode != kApply || l.last) ? l.max_count : (l.chip.cus / l.chip.xcds) * per_cu;
   const dim3 grid(unsigned(l.max_count < per_xcd ? l.max_count : per_xcd) * unsigned(l.chip.xcds));
-#define LM_LAUNCH_SYM(T, BT, NB, KG)                                                               \
+#define LM_LAUNCH_SYM(T, BT, NB)                                                               \
   do {                                                                                             \
-    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
-    if (mode == kGram) hipLaunchKernelGGL((ns_gram_kernel<T, BT, NB, KG>), full, block, 0, stream, a); \
-    else hipLaunchKernelGGL((ns_poly_kernel<T, BT, NB, KG>), full, block, 0, stream, a);           \
+    const dim3 block(block_threads<BT, NB>());                                                 \
+    if (mode == kGram) hipLaunchKernelGGL((ns_gram_kernel<T, BT, NB>), full, block, 0, stream, a); \
+    else hipLaunchKernelGGL((ns_poly_kernel<T, BT, NB>), full, block, 0, stream, a);           \
   } while (0)
-#define LM_LAUNCH_APPLY(T, BT, NB, KG)                                                             \
+#define LM_LAUNCH_APPLY(T, BT, NB)                                                             \
   do {                                                                                             \
-    const dim3 block(TileGeom<BT>::kThreads * KG);                                                 \
-    if (!l.last) hipLaunchKernelGGL((ns_apply_kernel<T, BT, NB, KG>), KG == 1 && sizeof(T) == 2 ? grid : full, block, 0, stream, a); \
-    else hipLaunchKernelGGL((ns_apply_last_kernel<T, BT, NB, KG>), full, block, 0, stream, a);     \
+    const dim3 block(block_threads<BT, NB>());                                                 \
+    if (!l.last) hipLaunchKernelGGL((ns_apply_kernel<T, BT, NB>), sizeof(T) == 2 ? grid : full, block, 0, stream, a); \
+    else hipLaunchKernelGGL((ns_apply_last_kernel<T, BT, NB>), full, block, 0, stream, a);     \
   } while (0)
   // one workgroup per tile, except the persistent apply
   const dim3 full(unsigned(l.max_count) * unsigned(l.chip.xcds));
-  const int variant = l.tile * 100 + l.bufs * 10 + l.groups;
+  const int variant = l.tile * 10 + l.bufs;
   if (l.fp32) {
     if (l.tile != 64 && l.tile != 128) return hipErrorInvalidValue;
     if (mode == kApply) {
-      if (l.tile == 64) LM_LAUNCH_APPLY(float, 64, 0, 1);
-      else LM_LAUNCH_APPLY(float, 128, 0, 1);
+      if (l.tile == 64) LM_LAUNCH_APPLY(float, 64, 0);
+      else LM_LAUNCH_APPLY(float, 128, 0);
     } else {
-      if (l.tile == 64) LM_LAUNCH_SYM(float, 64, 0, 1);
-      else LM_LAUNCH_SYM(float, 128, 0, 1);
+      if (l.tile == 64) LM_LAUNCH_SYM(float, 64, 0);
+      else LM_LAUNCH_SYM(float, 128, 0);
     }
   } else if (l.tile == 256) {
     if (mode == kApply && l.tail_max_count > 0) {
@@ -2270,19 +2319,19 @@ hipError_t launch_gemm(GemmMode mode, const GemmLaunch& l, hipStream_t stream) {
       }
 #undef LM_LAUNCH_PAIR
     } else {
-      if (mode == kApply) LM_LAUNCH_APPLY(bf16, 256, 0, 1);
-      else LM_LAUNCH_SYM(bf16, 256, 0, 1);
+      if (mode == kApply) LM_LAUNCH_APPLY(bf16, 256, 0);
+      else LM_LAUNCH_SYM(bf16, 256, 0);
     }
   } else {
     if (mode == kApply) {
-      if (variant == 12821) LM_LAUNCH_APPLY(bf16, 128, 2, 1);
-      else if (variant == 6421) LM_LAUNCH_APPLY(bf16, 64, 2, 1);
+      if (variant == 1282) LM_LAUNCH_APPLY(bf16, 128, 2);
+      else if (variant == 642) LM_LAUNCH_APPLY(bf16, 64, 2);
       else return hipErrorInvalidValue;
     } else {
-      if (variant == 12821) LM_LAUNCH_SYM(bf16, 128, 2, 1);
-      else if (variant == 6421) LM_LAUNCH_SYM(bf16, 64, 2, 1);
-      else if (variant == 6441) LM_LAUNCH_SYM(bf16, 64, 4, 1);
-      else if (variant == 6442) LM_LAUNCH_SYM(bf16, 64, 4, 2);
+      if (variant == 1282) LM_LAUNCH_SYM(bf16, 128, 2);
+      else if (variant == 642) LM_LAUNCH_SYM(bf16, 64, 2);
+      else if (variant == 644) LM_LAUNCH_SYM(bf16, 64, 4);
+      else if (variant == 648) LM_LAUNCH_SYM(bf16, 64, 8);
       else return hipErrorInvalidValue;
     }
   }

@@ -176,8 +176,8 @@ std::vector<int64_t> stages_of(const std::vector<MuonMat>& mats, const std::vect
 // are estimated to beat the tiles already chosen (`p->tile`), which fill the
 // chip on the large sets but leave most of it idle on a shard or a small
 // model: one 768 x 3072 matrix is 36 apply 256-tiles on 256 CUs. Measured
-// (us a launch, the usual tiles -> these): one 768 x 3072 matrix Gram 42 -> 14,
-// polynomial 15 -> 8, apply 28 -> 12; the four matrices of a 768-wide layer
+// (us a launch, the usual tiles -> these): one 768 x 3072 matrix Gram 42 -> 12,
+// polynomial 15 -> 7, apply 28 -> 12; the four matrices of a 768-wide layer
 // 42 -> 19, 15 -> 9, 29 -> 18; sixteen 256 x 1024 15 -> 7, 9 -> 5, 18 -> 9. At
 // two layers the apply's 256-tiles are level (31 against 34), at four all
 // three are; at twelve 64-tiles lose (Gram 86 -> 130, apply 168 -> 300).
@@ -194,14 +194,14 @@ void pick_fine(Plan* p, int pr, int st) {
     StageCost c;
     bool one_round;        // only where every tile gets a CU of its own
   };
-  static const Choice sym[] = {{{64, 4, 2, 1}, {20, 20, 150}, true},
-                               {{64, 4, 1, 2}, {27, 20, 150}, false},
-                               {{64, 2, 1, 4}, {46, 20, 150}, false},
-                               {{128, 2, 1, 2}, {78, 62, 250}, false}};
-  static const Choice app[] = {{{64, 2, 1, 4}, {46, 19, 150}, false},
-                               {{128, 2, 1, 2}, {85, 55, 300}, false}};
-  static const Choice f32[] = {{{64, 2, 1, 1}, {85, 85, 450}, false},
-                               {{128, 2, 1, 2}, {240, 265, 600}, false}};
+  static const Choice sym[] = {{{64, 8, 1}, {20, 20, 150}, true},
+                               {{64, 4, 2}, {27, 20, 150}, false},
+                               {{64, 2, 4}, {46, 20, 150}, false},
+                               {{128, 2, 2}, {78, 62, 250}, false}};
+  static const Choice app[] = {{{64, 2, 4}, {46, 19, 150}, false},
+                               {{128, 2, 2}, {85, 55, 300}, false}};
+  static const Choice f32[] = {{{64, 2, 1}, {85, 85, 450}, false},
+                               {{128, 2, 2}, {240, 265, 600}, false}};
   const StageCost big = st < 2 ? StageCost{150, 150, 500} : StageCost{200, 200, 400};
   const XcdSplit& msplit = st == 0 ? p->gram_split[0] : (st == 1 ? p->poly_split[0] : p->apply_split[0]);
   int64_t best = 0;

@@ -54,10 +54,10 @@ struct NsPrecision {
 // Appendix G made on the device.
 enum class StepKind : int { kLion = 0, kMuon = 1, kAdaptive = 2 };
 
-// One way to run a product in small tiles: tile edge, LDS stages, and groups
-// of waves that share a tile's K loop. `slots` such workgroups fit a CU.
+// One way to run a product in small tiles: tile edge and LDS stages; `slots`
+// such workgroups fit a CU.
 struct GemmVariant {
-  int32_t tile = 0, bufs = 2, groups = 1, slots = 1;
+  int32_t tile = 0, bufs = 2, slots = 1;
 };
 
 struct Plan {

@@ -35,7 +35,7 @@ int main(int argc, char** argv) {
     for (int st = 0; st < 3; ++st) {
       const GemmVariant& v = p.variant[pr][st];
       const std::vector<GemmTask>& list = p.fine[pr][st];
-      if (pr == 0) printf("%d/%d/%d ", v.tile, v.bufs, v.groups);
+      if (pr == 0) printf("%d/%d ", v.tile, v.bufs);
       if (v.tile == 0) {
         bad += !list.empty();
         continue;

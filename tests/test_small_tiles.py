@@ -3,7 +3,7 @@
 CPU: the planner's choice and its tile lists (``planner_small_tiles_driver.cpp``).
 GPU: Muon steps over the same lists against the oracle, at sides on both
 sides of a tile edge and K loops of one stage, of fewer stages than a tile has
-LDS buffers, and of an odd number for two wave groups.
+LDS buffers. A bf16 matrix has the same result, to the bit, in every list.
 """
 import os
 import shutil
@@ -15,17 +15,17 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2605_19811_amd", "csrc")
 
-# list of shapes -> "tile/LDS stages/wave groups" of Gram, polynomial, apply
+# list of shapes -> "tile/LDS stages" of Gram, polynomial, apply
 # (0: the usual tiles)
 LISTS = {
-    "one-stage": ([(64, 64)], "64/4/2 64/4/2 64/2/1"),
-    "edges": ([(65, 129), (129, 65), (127, 193), (64, 321)], "64/4/2 64/4/2 64/2/1"),
-    "one-wide": ([(300, 1000)], "64/4/2 64/4/2 64/2/1"),
-    "one-tall": ([(1089, 257)], "64/4/2 64/4/2 64/2/1"),
-    "two-per-cu": ([(500, 700), (700, 500)] * 5, "64/4/1 64/4/1 64/2/1"),
-    "apply-128": ([(768, 2304), (768, 768), (768, 3072), (3070, 766)], "64/4/1 64/4/1 128/2/1"),
-    "poly-two-stage": ([(2000, 2000)], "64/2/1 64/2/1 64/2/1"),
-    "gram-small-only": ([(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 3, "64/4/1 0/2/1 0/2/1"),
+    "one-stage": ([(64, 64)], "64/8 64/8 64/2"),
+    "edges": ([(65, 129), (129, 65), (127, 193), (64, 321)], "64/8 64/8 64/2"),
+    "one-wide": ([(300, 1000)], "64/8 64/8 64/2"),
+    "one-tall": ([(1089, 257)], "64/8 64/8 64/2"),
+    "two-per-cu": ([(500, 700), (700, 500)] * 5, "64/4 64/4 64/2"),
+    "apply-128": ([(768, 2304), (768, 768), (768, 3072), (3070, 766)], "64/4 64/4 128/2"),
+    "poly-two-stage": ([(2000, 2000)], "64/2 64/2 64/2"),
+    "gram-small-only": ([(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 3, "64/4 0/2 0/2"),
 }
 
 
@@ -62,6 +62,29 @@ def test_small_tiles_match_oracle(name):
     for i in range(len(shapes)):
         check_muon(W0[i], G[i], M0[i], W[i].cpu().double().numpy(), M[i].cpu().double().numpy(),
                    0.9, 0.99, 0.02, 0.1, "bf16")
+
+
+# A bf16 matrix alone and 40 or more of it in one call, which run in other tiles
+# (K loops of 1 to 48 stages, below and above the eight LDS stages of a tile
+# alone on its CU; edges of 64-tiles): each element's sum runs through K in
+# order in either, so the results are equal.
+SAME = {(64, 64): 512, (65, 448): 256, (96, 512): 256, (128, 577): 256, (256, 1024): 256,
+        (300, 1000): 192, (1000, 300): 192, (768, 3072): 40}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", sorted(SAME))
+def test_bf16_result_does_not_depend_on_the_list(shape):
+    import torch
+
+    from paper_2605_19811_amd import lionmuon as lm
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(shape[0])
+    x = torch.randn((SAME[shape], *shape), generator=gen, device="cuda")
+    cfg = lm.config()
+    many = lm.lionmuon_ns(x, cfg)
+    for i in (0, SAME[shape] - 1):
+        assert torch.equal(lm.lionmuon_ns(x[i].contiguous(), cfg), many[i])
 
 
 # fp32 products: K loops of 1 to 9 stages of 64 on 64-tiles (a round is 8), tile edges,
