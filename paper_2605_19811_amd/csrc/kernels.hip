@@ -206,6 +206,49 @@ __device__ __forceinline__ void load4(const float* p, float v[4]) {
 // LDS block of the transpose tile (bf16 64 x 131 or fp32 64 x 66 elements)
 constexpr int kPrepLdsBytes = 64 * 66 * 4;
 
+// Lane exchanges within a quad of lanes through DPP (no LDS traffic).
+__device__ __forceinline__ float dpp_quad_xor1(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1,
+                                                            0xF, 0xF, true));   // [1,0,3,2]
+}
+__device__ __forceinline__ float dpp_quad_xor2(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E,
+                                                            0xF, 0xF, true));   // [2,3,0,1]
+}
+
+// 4 x 4 transpose across the quad: lane b enters with v[e] = C[e][b] and
+// leaves with v[j] = C[b][j]. Two exchange rounds (partners b ^ 2, then
+// b ^ 1), each lane sending two values and receiving two.
+__device__ __forceinline__ void quad_transpose(float v[4], int b) {
+  const bool lo = b < 2;
+  float s0 = dpp_quad_xor2(lo ? v[2] : v[0]);
+  float s1 = dpp_quad_xor2(lo ? v[3] : v[1]);
+  if (lo) { v[2] = s0; v[3] = s1; } else { v[0] = s0; v[1] = s1; }
+  const bool even = (b & 1) == 0;
+  s0 = dpp_quad_xor1(even ? v[1] : v[0]);
+  s1 = dpp_quad_xor1(even ? v[3] : v[2]);
+  if (even) { v[1] = s0; v[3] = s1; } else { v[0] = s0; v[2] = s1; }
+}
+
+// First column, within the tile, of the four consecutive ones a lane holds of a
+// row in the end, and a lane's sum moved to where the aligned layout has it.
+// Off 16 bytes a lane reads columns c, c + kChunks, c + 2 kChunks, c + 3 kChunks;
+// the transpose within its quad then gives lane 4 Q + b columns 4 (b kChunks / 4
+// + Q) and the next three, the ones that lane b kChunks / 4 + Q reads of aligned
+// rows. So the squares are summed in one order wherever a matrix starts, and
+// its result does not depend on it.
+template <int kChunks, bool VEC>
+__device__ __forceinline__ int prep_col(int tid) {
+  const int c = tid % kChunks;
+  return 4 * (VEC ? c : (c & 3) * (kChunks / 4) + (c >> 2));
+}
+template <int kChunks, bool VEC>
+__device__ __forceinline__ float prep_order(float ss, int tid) {
+  if constexpr (VEC) return ss;
+  const int lane = tid & 63, c = lane % kChunks;
+  return __shfl(ss, lane - c + 4 * (c % (kChunks / 4)) + c / (kChunks / 4));
+}
+
 // Wide matrix (X = Ghat, same layout): a strip of kPrepElems elements, TC
 // columns wide, so that each wave reads and writes whole TC-element pieces
 // of rows (1 KB of fp32 for TC = 256). G and M are read and M written with
@@ -264,7 +307,6 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
     for (int e = 0; e < 4; ++e) {
       c[e] = fmaf(a.b1, mv[e], a.omb1 * gv[e]);
       mn[e] = fmaf(a.b2, mv[e], a.omb2 * gv[e]);
-      ss = fmaf(c[e], c[e], ss);
     }
     if (Mp) {
       if (vec) {
@@ -276,14 +318,12 @@ __device__ __forceinline__ void prep_wide(const PrepArgs& a, const MuonMat& mm, 
           if (q + kStep * e < mm.cols) Mp[idx + kStep * e] = mn[e];
       }
     }
-    if constexpr (VEC) {
-      store4(X + p * cols_pad + q, c);
-    } else {
+    if constexpr (!VEC) quad_transpose(c, tid & 3);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) X[p * cols_pad + q + kStep * e] = to_elem<T>(c[e]);
-    }
+    for (int e = 0; e < 4; ++e) ss = fmaf(c[e], c[e], ss);
+    store4(X + p * cols_pad + int64_t(tj) * TC + prep_col<kChunks, VEC>(tid), c);
   }
-  ss = wave_sum(ss);
+  ss = wave_sum(prep_order<kChunks, VEC>(ss, tid));
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
   if (tid == 0) a.partials[mm.prep_first + local] = (red[0] + red[1]) + (red[2] + red[3]);
@@ -343,7 +383,6 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
     for (int e = 0; e < 4; ++e) {
       c[e] = fmaf(a.b1, mv[e], a.omb1 * gv[e]);
       mn[e] = fmaf(a.b2, mv[e], a.omb2 * gv[e]);
-      ss = fmaf(c[e], c[e], ss);
     }
     if (Mp) {
       if (vec) {
@@ -357,6 +396,9 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) tile[r][c4 + kStep * e] = to_elem<T>(c[e]);
+    if constexpr (!VEC) quad_transpose(c, tid & 3);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ss = fmaf(c[e], c[e], ss);
   }
   __syncthreads();
   // X^T rows: kTC of them, kTR elements each, 4 per thread
@@ -370,7 +412,7 @@ __device__ __forceinline__ void prep_tall(const PrepArgs& a, const MuonMat& mm, 
     for (int e = 0; e < 4; ++e) v[e] = float(tile[xc4 + e][qq]);
     store4(X + (int64_t(tj) * kTC + qq) * rows_pad + int64_t(ti) * kTR + xc4, v);
   }
-  ss = wave_sum(ss);
+  ss = wave_sum(prep_order<kChunks, VEC>(ss, tid));
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
   if (tid == 0) a.partials[mm.prep_first + local] = (red[0] + red[1]) + (red[2] + red[3]);
@@ -998,30 +1040,6 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-}
-
-// Lane exchanges within a quad of lanes through DPP (no LDS traffic).
-__device__ __forceinline__ float dpp_quad_xor1(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1,
-                                                            0xF, 0xF, true));   // [1,0,3,2]
-}
-__device__ __forceinline__ float dpp_quad_xor2(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E,
-                                                            0xF, 0xF, true));   // [2,3,0,1]
-}
-
-// 4 x 4 transpose across the quad: lane b enters with v[e] = C[e][b] and
-// leaves with v[j] = C[b][j]. Two exchange rounds (partners b ^ 2, then
-// b ^ 1), each lane sending two values and receiving two.
-__device__ __forceinline__ void quad_transpose(float v[4], int b) {
-  const bool lo = b < 2;
-  float s0 = dpp_quad_xor2(lo ? v[2] : v[0]);
-  float s1 = dpp_quad_xor2(lo ? v[3] : v[1]);
-  if (lo) { v[2] = s0; v[3] = s1; } else { v[0] = s0; v[1] = s1; }
-  const bool even = (b & 1) == 0;
-  s0 = dpp_quad_xor1(even ? v[1] : v[0]);
-  s1 = dpp_quad_xor1(even ? v[3] : v[2]);
-  if (even) { v[1] = s0; v[3] = s1; } else { v[0] = s0; v[2] = s1; }
 }
 
 // Scheduling directives for the MFMA k-steps of one stage: NM MFMAs with the

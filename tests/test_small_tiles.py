@@ -148,3 +148,25 @@ def test_rows_off_16_bytes(shape, prec, tol):
         assert torch.isnan(flat[0]) and torch.isnan(flat[-1])
     check_muon(W0, G, M0, W.cpu().double().numpy(), M.cpu().double().numpy(),
                0.9, 0.99, 0.02, 0.1, prec)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+@pytest.mark.parametrize("shape", [(65, 132), (64, 600), (300, 1000), (132, 68), (600, 200), (1000, 300)])
+def test_result_does_not_depend_on_where_a_matrix_starts(shape, prec):
+    """The same step on 16-byte aligned buffers and on buffers one float off:
+    every sum has one order, so W and M are equal to the bit."""
+    import torch
+
+    from paper_2605_19811_amd import lionmuon as lm
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(shape[0])
+    x = [torch.randn(shape, generator=gen, device="cuda") * std for std in (0.02, 1e-2, 1e-2)]
+    cfg = lm.config(ns_precision=prec, lr_muon=0.02)
+    out = []
+    for shift in (0, 1):
+        W, G, M = (torch.empty(v.numel() + 4, device="cuda")[shift:shift + v.numel()].view(shape).copy_(v)
+                   for v in x)
+        lm.lionmuon_step_ex([W], [G], [M], 0, 1, 0.9, 0.99, 0.1, cfg)
+        out.append((W, M))
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][0], out[1][0])
