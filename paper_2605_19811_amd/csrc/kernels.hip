@@ -28,6 +28,7 @@ namespace {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -1063,14 +1064,13 @@ __device__ __forceinline__ void sched_interleave() {
   }
 }
 
-// N times one MFMA, then V vector operations and R LDS reads.
-template <int N, int V, int R>
+// N times one MFMA, then V vector operations.
+template <int N, int V>
 __device__ __forceinline__ void sched_split() {
   if constexpr (N > 0) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
-    if constexpr (R > 0) __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
-    sched_split<N - 1, V, R>();
+    sched_split<N - 1, V>();
   }
 }
 
@@ -1089,11 +1089,16 @@ template <> struct Mfma<bf16> {
 };
 
 // fp32 products on the bf16 matrix instruction: each fp32 operand x is the
-// exact sum of three bf16 values, x = h + m + l, the upper, middle and lower
-// eight bits of its significand, and the product keeps the six terms down to
-// 2^-16 of the largest (hh; hm, mh; hl, lh, mm), so what it drops (ml, lm, ll)
-// is at most 2^-22 (typically 2^-25) of a term, below the rounding of an fp32
-// product. Six 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32
+// exact sum of three bf16 values, x = h + m + l, each what is left of x rounded
+// to nearest, so that |m| <= 2^-8 |x| and |l| <= 2^-17 |x|. The product keeps the
+// six terms down to 2^-16 of the largest (hh; hm, mh; hl, lh, mm); what it drops
+// (ml, lm, ll) has either sign and is at most 2^-24 of the product, the rounding
+// of an fp32 product (2^-27.5 root mean square). Parts cut off instead of
+// rounded all have the sign of x: 2^-21, always towards zero, and twice the error
+// at short sides of 2 to 16 (1.0e-6 after five steps; now 5.0e-7, by fp32 MFMAs
+// 5.2e-7). A value from 2^128 (1 - 2^-9) on would round to infinity: only
+// coefficients of that size bring one, and its Gram product is infinite anyway.
+// Six 32x32x16 bf16 MFMAs take 192 cycles where eight 32x32x2 fp32
 // ones took 512. The operands stay fp32 in memory and in LDS and are split in
 // registers (44 vector operations a fragment).
 template <> struct Mfma<float> {
@@ -1102,23 +1107,22 @@ template <> struct Mfma<float> {
   struct Frag {
     u32x4 h, m, l;
   };
-  // Eight values of a lane. Each part is the upper 16 bits of what is left of
-  // the value (truncated, so the remainder is exact).
+  // Two values rounded to bf16, and what that leaves of them.
+  __device__ static __forceinline__ uint32_t part(f32x2& x) {
+    const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+    x[0] -= __builtin_bit_cast(float, p << 16);
+    x[1] -= __builtin_bit_cast(float, p & 0xffff0000u);
+    return p;
+  }
+  // Eight values of a lane.
   __device__ static __forceinline__ Frag split(const float x[8]) {
     Frag f;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      uint32_t u[2], v[2], w[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        u[e] = __builtin_bit_cast(uint32_t, x[2 * p + e]);
-        const float r = x[2 * p + e] - __builtin_bit_cast(float, u[e] & 0xffff0000u);
-        v[e] = __builtin_bit_cast(uint32_t, r);
-        w[e] = __builtin_bit_cast(uint32_t, r - __builtin_bit_cast(float, v[e] & 0xffff0000u));
-      }
-      f.h[p] = __builtin_amdgcn_perm(u[1], u[0], 0x07060302u);
-      f.m[p] = __builtin_amdgcn_perm(v[1], v[0], 0x07060302u);
-      f.l[p] = __builtin_amdgcn_perm(w[1], w[0], 0x07060302u);
+      f32x2 r = {x[2 * p], x[2 * p + 1]};
+      f.h[p] = part(r);
+      f.m[p] = part(r);
+      f.l[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
     }
     return f;
   }
@@ -1224,9 +1228,11 @@ __device__ __forceinline__ void copy16(const T* src, uint32_t off, const T* dst)
 // step before run, which the barrier in mid-stage
 // allows (it publishes the next stage). The matrix unit truncates where it adds
 // to its accumulator: the products of each 128 K values start from zero, and
-// vector adds collect them (1000 x 3000 matrix, five steps: 1.1e-6 from 64 bits,
-// 1.0e-5 with one accumulator over the whole K loop, 3.3e-6 by fp32 MFMAs). Two
-// 1000 x 3000: Gram 109 -> 81 us, apply 135 -> 89.
+// vector adds collect them (1000 x 3000 matrix, five steps: 7e-7 from 64 bits,
+// 1.0e-5 with one accumulator over the whole K loop, 3.3e-6 by fp32 MFMAs), and the
+// first step's largest term goes to the outer sum, so that a K loop of one step
+// rounds its sum where it would truncate it (4-10% of the error at sides of 2 to 6). Two
+// 1000 x 3000: Gram 109 -> 84 us, apply 135 -> 89.
 template <int MODE, int BT>
 __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* smem, int tid, f32x16 (&out)[BT / 64][BT / 64]) {
   using M = Mfma<float>;
@@ -1303,7 +1309,8 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
   // in four parts, each with the split of one fragment of the next step
   // (kt1, kk1) between its MFMAs, and, where `ahead` >= 0, two of the eight
   // copies of stage `ahead` behind it: in one place they stalled the wave
-  // until the memory pipeline had taken them.
+  // until the memory pipeline had taken them. `fresh`: 0 adds to `part`, 1 and 2
+  // start it from zero (2: the first step of the K loop).
   auto step = [&](int slot, int kt1, int kk1, int ahead, auto fresh) {
     // (128-tiles read a fragment one part ahead: with all four in registers two
     // workgroups to a CU did not fit without spills)
@@ -1319,10 +1326,14 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
 #pragma unroll
       for (int m = 6 * r; m < 6 * r + 6; ++m) {
         const int t = m >> 2, i = (m >> 1) & 1, j = m & 1;
-        part[i][j] = M::term(t, fa[slot][i], fb[slot][j], decltype(fresh)::value && t == 0 ? f32x16(0.0f) : part[i][j]);
+        constexpr int kFresh = decltype(fresh)::value;
+        if (kFresh >= (BT == 128 ? 1 : 2) && t == M::kTerms - 1)
+          acc[i][j] = M::term(t, fa[slot][i], fb[slot][j], BT == 128 ? acc[i][j] : f32x16(0.0f));
+        else
+          part[i][j] = M::term(t, fa[slot][i], fb[slot][j], kFresh && t == 0 ? f32x16(0.0f) : part[i][j]);
       }
       split(slot ^ 1, r);
-      sched_split<6, 7, 0>();
+      sched_split<6, 7>();
       __builtin_amdgcn_sched_barrier(0);
       if (ahead >= 0) {
         copy1(ahead, 2 * r);
@@ -1340,7 +1351,7 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
     __builtin_amdgcn_sched_barrier(0);
   };
   auto stage = [&](int par, int kt, auto fresh) {
-    if (decltype(fresh)::value) fold();
+    if (decltype(fresh)::value == 1) fold();
     if constexpr (kSub == 2) {
       step(0, kt, 1, -1, fresh);
       next_stage();
@@ -1360,15 +1371,27 @@ __device__ __forceinline__ void split_product(const GemmOps<float>& o, float* sm
     split(0, f);
   }
   // rounds of 128 K values to a wave, each into `part` from zero; the tail of
-  // the last round one pair of stages at a time
+  // the last round one pair of stages at a time. The largest term of a step that
+  // starts from zero goes to `acc`: on 64-tiles the first step's only, ahead of the
+  // loop (in every round, `acc` would live in the accumulation registers: 4%
+  // slower), on 128-tiles every round's (the other form spills 27 registers).
   constexpr int kRound = BT == 128 ? 4 : 8;
   int kt = 0;
-  for (; kt + kRound <= nk; kt += kRound) {
-    stage(0, kt, Const<1>());
+  if constexpr (BT == 64) {
+    stage(0, kt++, Const<2>());
+    for (; kt + kRound <= nk; kt += kRound) {
 #pragma unroll
-    for (int i = 1; i < kRound; ++i) stage(i & 1, kt + i, Const<0>());
+      for (int i = 0; i < kRound - 1; ++i) stage((i + 1) & 1, kt + i, Const<0>());
+      stage(0, kt + kRound - 1, Const<1>());
+    }
+  } else {
+    for (; kt + kRound <= nk; kt += kRound) {
+      stage(0, kt, Const<1>());
+#pragma unroll
+      for (int i = 1; i < kRound; ++i) stage(i & 1, kt + i, Const<0>());
+    }
+    if (kt < nk) stage(0, kt++, Const<1>());
   }
-  if (kt < nk) stage(0, kt++, Const<1>());
   for (; kt + 2 <= nk; kt += 2) {
     stage(1, kt, Const<0>());
     stage(0, kt + 1, Const<0>());

@@ -119,6 +119,33 @@ def test_split_fp32_products_match_oracle(name):
                    0.9, 0.99, 0.02, 0.1, "fp32")
 
 
+def newton_schulz_batch(x, dtype):
+    """Five quintic steps of a batch of wide matrices in plain numpy."""
+    a, b, c = (dtype(v) for v in (3.4445, -4.7750, 2.0315))
+    norm = np.sqrt(np.square(x.astype(np.float64)).sum((1, 2), keepdims=True)) + 1e-7
+    x = x.astype(dtype) / norm.astype(dtype)
+    for _ in range(5):
+        g = x @ x.transpose(0, 2, 1)
+        x = (a * np.eye(x.shape[1], dtype=dtype) + (b * g + c * (g @ g))) @ x
+    return x.astype(np.float64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("count", [1500, 2500])          # 64-tiles, 128-tiles
+@pytest.mark.parametrize("shape", [(2, 3), (2, 64), (3, 17), (4, 8), (8, 16), (16, 150), (48, 96)])
+def test_fp32_products_are_as_exact_as_32_bit_sums(shape, count):
+    """Short sides, where dropped parts of a product show most: over many
+    matrices, no further from 64 bits than the recursion in 32-bit numpy is."""
+    import torch
+
+    from paper_2605_19811_amd import lionmuon as lm
+    count //= max(1, shape[0] * shape[1] // 1000)        # (the large ones: fewer do)
+    x = np.random.default_rng(shape[0]).standard_normal((count, *shape)).astype(np.float32)
+    o = lm.lionmuon_ns(torch.from_numpy(x).cuda(), lm.config(ns_precision="fp32")).cpu().double().numpy()
+    ref = newton_schulz_batch(x, np.float64)
+    assert np.linalg.norm(o - ref) <= np.linalg.norm(newton_schulz_batch(x, np.float32) - ref)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("prec,tol", [("bf16", 2e-2), ("fp32", 1e-4)])
 @pytest.mark.parametrize("shape", [(65, 131), (131, 65), (200, 333), (333, 200)])
