@@ -105,7 +105,7 @@ StagingRing g_ring;
 // binding table (one TensorPtrs per input tensor), rewritten on the call's
 // stream whenever a call brings other tensor addresses than the previous
 // call of the plan.
-constexpr int kTaskLists = 7;
+constexpr int kTaskLists = 4;
 
 struct DevicePlan {
   Plan plan;
@@ -124,7 +124,7 @@ struct DevicePlan {
   lm::SrBlock* d_sr_tab = nullptr;
   int32_t* d_rd_start = nullptr;
   int32_t* d_tensor_mat = nullptr;
-  // [precision][gram, poly, apply, apply tail, fine gram, fine poly, fine apply]
+  // [precision][gram, poly, apply, apply tail]: the lists the launches run
   lm::GemmTask* d_tasks[2][kTaskLists] = {};
   lm::XcdSplit* d_splits = nullptr;   // [precision * kTaskLists + list]
 
@@ -298,20 +298,20 @@ void pack_tables(Plan& p, std::vector<lm::TensorPtrs>& bind, TableImage* img) {
   img->o_sr = off;         place(p.sr_tab, &off, &parts);
   img->o_rd = off;         place(p.rd_start, &off, &parts);
   img->o_tm = off;         place(p.tensor_mat, &off, &parts);
+  // of each product the list that its launches run: small tiles, or the usual ones
   std::vector<lm::XcdSplit> splits;
+  std::vector<lm::GemmTask> none;
   for (int pr = 0; pr < 2; ++pr) {
-    img->o_tasks[pr][0] = off; place(p.gram[pr], &off, &parts);
-    img->o_tasks[pr][1] = off; place(p.poly[pr], &off, &parts);
-    img->o_tasks[pr][2] = off; place(p.apply[pr], &off, &parts);
-    img->o_tasks[pr][3] = off; place(p.apply_tail[pr], &off, &parts);
-    splits.push_back(p.gram_split[pr]);
-    splits.push_back(p.poly_split[pr]);
-    splits.push_back(p.apply_split[pr]);
-    splits.push_back(p.apply_tail_split[pr]);
+    std::vector<lm::GemmTask>* usual[3] = {&p.gram[pr], &p.poly[pr], &p.apply[pr]};
+    const lm::XcdSplit* usual_split[3] = {&p.gram_split[pr], &p.poly_split[pr], &p.apply_split[pr]};
     for (int st = 0; st < 3; ++st) {
-      img->o_tasks[pr][4 + st] = off; place(p.fine[pr][st], &off, &parts);
-      splits.push_back(p.fine_split[pr][st]);
+      const bool fine = p.variant[pr][st].tile > 0;
+      img->o_tasks[pr][st] = off; place(fine ? p.fine[pr][st] : *usual[st], &off, &parts);
+      splits.push_back(fine ? p.fine_split[pr][st] : *usual_split[st]);
     }
+    const bool tail = p.variant[pr][2].tile == 0;
+    img->o_tasks[pr][3] = off; place(tail ? p.apply_tail[pr] : none, &off, &parts);
+    splits.push_back(tail ? p.apply_tail_split[pr] : lm::XcdSplit{});
   }
   img->o_splits = off;     place(splits, &off, &parts);
   img->bytes.assign(std::max<size_t>(off, 256), 0);
@@ -622,9 +622,8 @@ lm_status enqueue(const DevicePlan& dp, const lm::StepConsts& k, const lm_config
                                       : (st3 == 0 ? p.gram_split[pr]
                                                   : (st3 == 1 ? p.poly_split[pr] : p.apply_split[pr]));
         if (sp.max_count == 0) continue;
-        const int list = fine ? 4 + st3 : st3;
-        gl.tasks = dp.d_tasks[pr][list];
-        gl.split = dp.d_splits + pr * kTaskLists + list;
+        gl.tasks = dp.d_tasks[pr][st3];
+        gl.split = dp.d_splits + pr * kTaskLists + st3;
         gl.max_count = sp.max_count;
         gl.fp32 = pr;
         gl.tile = fine ? v.tile : p.tile[pr][st3];
@@ -831,7 +830,7 @@ lm_status step_noalloc_impl(float* const* params, const float* const* grads,
     TableImage img;
     pack_tables(p, bind, &img);
     if (align256(img.bytes.size()) + p.ws_bytes > lm::kScratchBytes) {
-      lm::drop_fine(&p);                   // the usual tiles need no tables of their own
+      lm::drop_fine(&p);                   // the usual tiles are fewer
       pack_tables(p, bind, &img);
     }
     const size_t ws_off = align256(img.bytes.size());
@@ -991,7 +990,7 @@ lm_status lionmuon_plan_info(const lm_shape* shapes, int32_t n, int64_t t, int32
   if (st != Status::kOk) return fail(to_c(st), err);
   Plan p;
   st = lm::build_plan(x.data(), n, step_kind(*cfg, t, P), precision_of(*cfg),
-                      cfg->ns_scale_mode == LM_NS_SCALE_RMS02, current_chip(), &p, &err);
+                      cfg->ns_scale_mode == LM_NS_SCALE_RMS02, current_chip(), &p, &err, false);
   if (st != Status::kOk) return fail(to_c(st), err);
   std::memset(out, 0, sizeof(*out));
   out->n_tensors = p.n_tensors;

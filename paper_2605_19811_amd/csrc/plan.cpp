@@ -4,10 +4,8 @@
 #include <algorithm>
 #include <cstdint>
 #include <cmath>
-#include <functional>
 #include <map>
 #include <numeric>
-#include <queue>
 #include <utility>
 
 namespace lm {
@@ -117,6 +115,24 @@ void fine_tiles(const std::vector<MuonMat>& mats, int fp32, int st, int tile,
   }
 }
 
+// Neighbouring tiles of one cost (a matrix's tiles of one product).
+struct Run {
+  int64_t stages, n;
+};
+
+// A product's tiles of `tile`, matrix by matrix: the list of fine_tiles.
+std::vector<Run> fine_runs(const std::vector<MuonMat>& mats, int fp32, int st, int tile) {
+  std::vector<Run> r;
+  for (const MuonMat& mm : mats) {
+    if (mm.fp32 != fp32) continue;
+    const int64_t ts = (mm.s + tile - 1) / tile, tl = (mm.l + tile - 1) / tile;
+    const int64_t stages = ((st == 0 ? mm.l : mm.s) + 63) / 64, n = st < 2 ? ts * (ts + 1) / 2 : ts * tl;
+    if (!r.empty() && r.back().stages == stages) r.back().n += n;
+    else r.push_back({stages, n});
+  }
+  return r;
+}
+
 // Estimated time (units of 10 ns, past what every launch costs) of one
 // launch: each XCD's tiles, longest first, go to its least loaded CU, which
 // runs `slots` of them at a time. A K stage takes `alone` in a workgroup that
@@ -127,49 +143,109 @@ void fine_tiles(const std::vector<MuonMat>& mats, int fp32, int st, int tile,
 struct StageCost {
   int64_t alone, shared, fixed;
 };
-int64_t launch_estimate(const std::vector<int64_t>& stages, const XcdSplit& split, int slots,
-                        StageCost c, ChipShape chip) {
+int64_t xcd_estimate(const std::vector<Run>& runs, int slots, StageCost c, int64_t cus) {
   struct Cu {
     int64_t load, sum, longest, done;   // stages assigned; the current group's; finished groups' time
     int n;
   };
-  const int cus = std::max(1, chip.cus / chip.xcds);
-  auto group = [&](const Cu& u) {
-    return u.n == 0 ? 0 : std::max(u.longest * c.alone, u.sum * c.shared) + c.fixed;
+  auto time = [&](const Cu& u) {
+    return u.done + (u.n == 0 ? 0 : std::max(u.longest * c.alone, u.sum * c.shared) + c.fixed);
   };
-  int64_t worst = 0;
-  for (int x = 0; x < chip.xcds; ++x) {
-    auto more = [](const Cu& a, const Cu& b) { return a.load > b.load; };
-    std::priority_queue<Cu, std::vector<Cu>, decltype(more)> q(more);
-    for (int i = 0; i < cus; ++i) q.push(Cu{0, 0, 0, 0, 0});
-    for (int32_t i = split.start[x]; i < split.start[x] + split.count[x]; ++i) {
-      Cu u = q.top();
-      q.pop();
-      if (u.n == slots) {
-        u.done += group(u);
-        u.sum = u.longest = u.n = 0;
-      }
-      const int64_t k = stages[size_t(i)];
-      u.load += k;
-      u.sum += k;
-      u.longest = std::max(u.longest, k);
-      ++u.n;
-      q.push(u);
+  auto give = [&](Cu* u, int64_t k) {
+    if (u->n == slots) {
+      u->done = time(*u);
+      u->sum = u->longest = u->n = 0;
     }
-    for (; !q.empty(); q.pop()) worst = std::max(worst, q.top().done + group(q.top()));
+    u->load += k;
+    u->sum += k;
+    u->longest = std::max(u->longest, k);
+    ++u->n;
+  };
+  auto more = [](const Cu& a, const Cu& b) { return a.load > b.load; };
+  Cu each{};                 // every CU, as long as all have the same tiles
+  std::vector<Cu> q;         // then one by one, a heap by load
+  for (const Run& r : runs) {
+    int64_t n = r.n;
+    if (q.empty()) {
+      for (; n >= cus; n -= cus) give(&each, r.stages);
+      if (n > 0) q.assign(size_t(cus), each);
+    }
+    for (; n > 0; --n) {
+      std::pop_heap(q.begin(), q.end(), more);
+      give(&q.back(), r.stages);
+      std::push_heap(q.begin(), q.end(), more);
+    }
+  }
+  int64_t worst = q.empty() ? time(each) : 0;
+  for (const Cu& u : q) worst = std::max(worst, time(u));
+  return worst;
+}
+
+// The same of a whole launch whose tiles are dealt to the XCDs as split_by_xcd
+// does it. No list is built: it would take longer than the estimate.
+int64_t launch_estimate(const std::vector<Run>& runs, int slots, StageCost c, ChipShape chip) {
+  int64_t total = 0, given = 0, worst = 0;
+  for (const Run& r : runs) total += r.stages * r.n;
+  std::vector<Run> here, last;
+  size_t i = 0;
+  int64_t used = 0;          // tiles of runs[i] dealt
+  for (int x = 0; x < chip.xcds; ++x) {
+    const int64_t goal = (total * (x + 1) + chip.xcds - 1) / chip.xcds;
+    here.clear();
+    while (i < runs.size() && (given < goal || x == chip.xcds - 1)) {
+      const int64_t k = runs[i].stages, left = runs[i].n - used;
+      const int64_t m = x == chip.xcds - 1 ? left : std::min(left, (goal - given + k - 1) / k);
+      here.push_back({k, m});
+      given += m * k;
+      used += m;
+      if (used == runs[i].n) {
+        ++i;
+        used = 0;
+      }
+    }
+    auto longer = [](const Run& a, const Run& b) { return a.stages > b.stages; };
+    std::stable_sort(here.begin(), here.end(), longer);
+    auto same = [](const Run& a, const Run& b) { return a.stages == b.stages && a.n == b.n; };
+    if (here.size() == last.size() && std::equal(here.begin(), here.end(), last.begin(), same)) continue;
+    worst = std::max(worst, xcd_estimate(here, slots, c, std::max(1, chip.cus / chip.xcds)));
+    last = here;
   }
   return worst;
 }
 
-// The K stages of a split list's tasks, in list order.
-std::vector<int64_t> stages_of(const std::vector<MuonMat>& mats, const std::vector<GemmTask>& tasks,
-                               int st) {
-  std::vector<int64_t> c(tasks.size());
-  for (size_t i = 0; i < tasks.size(); ++i) {
-    const MuonMat& mm = mats[size_t(tasks[i].mat)];
-    c[i] = ((st == 0 ? mm.l : mm.s) + 63) / 64;
+// The same of a list that has been built and split.
+int64_t list_estimate(const std::vector<MuonMat>& mats, const std::vector<GemmTask>& tasks, int st,
+                      const XcdSplit& split, int slots, StageCost c, ChipShape chip) {
+  int64_t worst = 0;
+  std::vector<Run> here, last;
+  for (int x = 0; x < chip.xcds; ++x) {
+    here.clear();
+    for (int32_t i = split.start[x]; i < split.start[x] + split.count[x]; ++i) {
+      const MuonMat& mm = mats[size_t(tasks[size_t(i)].mat)];
+      const int64_t stages = ((st == 0 ? mm.l : mm.s) + 63) / 64;
+      if (!here.empty() && here.back().stages == stages) ++here.back().n;
+      else here.push_back({stages, 1});
+    }
+    auto same = [](const Run& a, const Run& b) { return a.stages == b.stages && a.n == b.n; };
+    if (here.size() == last.size() && std::equal(here.begin(), here.end(), last.begin(), same)) continue;
+    worst = std::max(worst, xcd_estimate(here, slots, c, std::max(1, chip.cus / chip.xcds)));
+    last = here;
   }
-  return c;
+  return worst;
+}
+
+// What launch_estimate cannot fall below: the mean of the CUs' times at the
+// shared rate, and the longest tile's. On large sets every variant loses by this
+// alone.
+int64_t launch_bound(const std::vector<Run>& runs, int slots, StageCost c, ChipShape chip) {
+  int64_t n = 0, sum = 0, longest = 0;
+  for (const Run& r : runs) {
+    n += r.n;
+    sum += r.n * r.stages;
+    longest = std::max(longest, r.stages);
+  }
+  const int64_t cus = int64_t(std::max(1, chip.cus / chip.xcds)) * chip.xcds;
+  return std::max((sum * c.shared + n / slots * c.fixed) / cus, longest * c.alone + c.fixed);
 }
 
 // Small tiles for one bf16 product (st: Gram, polynomial, apply) where they
@@ -188,6 +264,9 @@ std::vector<int64_t> stages_of(const std::vector<MuonMat>& mats, const std::vect
 void pick_fine(Plan* p, int pr, int st) {
   const std::vector<GemmTask>& macro = st == 0 ? p->gram[pr] : (st == 1 ? p->poly[pr] : p->apply[pr]);
   const size_t cus = size_t(p->chip.cus);
+  // (From eight rounds of the usual tiles on the chip is full, and no small tile
+  // was ever estimated or measured faster in bf16. fp32 lists that long keep
+  // their 128-tiles: the constants were fitted to shorter ones.)
   if (macro.empty() || macro.size() >= 8 * cus || p->chip.cus < p->chip.xcds) return;
   struct Choice {
     GemmVariant v;
@@ -208,30 +287,32 @@ void pick_fine(Plan* p, int pr, int st) {
   if (pr == 1) {
     best = INT64_MAX / 108;                // (the usual tiles cover the padding too)
   } else if (p->tile[0][st] == kTileBig) {
-    best = launch_estimate(stages_of(p->mats, macro, st), msplit, 1, big, p->chip);
+    best = list_estimate(p->mats, macro, st, msplit, 1, big, p->chip);
     // the apply's first start and last store, and the last round's small tiles
     if (st == 2) best += p->apply_tail[0].empty() ? 300 : 600;
   } else {
-    best = launch_estimate(stages_of(p->mats, macro, st), msplit, 2, sym[3].c, p->chip);
+    best = list_estimate(p->mats, macro, st, msplit, 2, sym[3].c, p->chip);
   }
   const Choice* first = pr == 1 ? f32 : (st < 2 ? sym : app);
+  const Choice* took = nullptr;
   for (const Choice* k = first; k != first + (first == sym ? 4 : 2); ++k) {
-    const GemmVariant v = k->v;
-    const StageCost c = k->c;
-    std::vector<GemmTask> tasks;
-    std::vector<int64_t> cost;
-    fine_tiles(p->mats, pr, st, v.tile, &tasks, &cost);
-    if (k->one_round && tasks.size() > cus) continue;
-    XcdSplit split;
-    split_by_xcd(&tasks, cost, p->chip.xcds, &split);
-    const int64_t est = launch_estimate(stages_of(p->mats, tasks, st), split, v.slots, c, p->chip);
+    const std::vector<Run> runs = fine_runs(p->mats, pr, st, k->v.tile);
+    int64_t n = 0;
+    for (const Run& r : runs) n += r.n;
+    if (k->one_round && n > int64_t(cus)) continue;
     // 8% less, or the tiles stay as they are: about the spread between boxes
-    if (est * (pr == 1 ? 100 : 108) >= best * 100) continue;
+    const int64_t need = pr == 1 ? 100 : 108;
+    if (launch_bound(runs, k->v.slots, k->c, p->chip) * need >= best * 100) continue;
+    const int64_t est = launch_estimate(runs, k->v.slots, k->c, p->chip);
+    if (est * need >= best * 100) continue;
     best = est;
-    p->variant[pr][st] = v;
-    p->fine[pr][st].swap(tasks);
-    p->fine_split[pr][st] = split;
+    took = k;
   }
+  if (!took) return;
+  std::vector<int64_t> cost;
+  p->variant[pr][st] = took->v;
+  fine_tiles(p->mats, pr, st, took->v.tile, &p->fine[pr][st], &cost);
+  split_by_xcd(&p->fine[pr][st], cost, p->chip.xcds, &p->fine_split[pr][st]);
 }
 
 }  // namespace
@@ -377,8 +458,9 @@ void split_by_xcd(std::vector<GemmTask>* tasks, const std::vector<int64_t>& cost
   for (int x = 0; x < xcds; ++x) {
     std::vector<size_t> idx(cut[x + 1] - cut[x]);
     std::iota(idx.begin(), idx.end(), cut[x]);
-    std::stable_sort(idx.begin(), idx.end(),
-                     [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+    auto longer = [&](size_t a, size_t b) { return cost[a] > cost[b]; };
+    if (!std::is_sorted(idx.begin(), idx.end(), longer))
+      std::stable_sort(idx.begin(), idx.end(), longer);
     split->start[x] = int32_t(out.size());
     split->count[x] = int32_t(idx.size());
     split->max_count = std::max(split->max_count, split->count[x]);
@@ -388,7 +470,7 @@ void split_by_xcd(std::vector<GemmTask>* tasks, const std::vector<int64_t>& cost
 }
 
 Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
-                  bool kappa_rms02, ChipShape chip, Plan* p, std::string* err) {
+                  bool kappa_rms02, ChipShape chip, Plan* p, std::string* err, bool small_tiles) {
   *p = Plan();
   if (chip.xcds < 1 || chip.xcds > kMaxXcds || chip.cus < chip.xcds) {
     *err = "unsupported device shape (compute units / XCDs)";
@@ -571,7 +653,7 @@ Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
     split_by_xcd(&p->apply[pr], ca, chip.xcds, &p->apply_split[pr]);
     split_by_xcd(&p->apply_tail[pr], ct, chip.xcds, &p->apply_tail_split[pr]);
   }
-  for (int pr = 0; pr < 2; ++pr)
+  for (int pr = 0; small_tiles && pr < 2; ++pr)
     for (int st = 0; st < 3; ++st) pick_fine(p, pr, st);
 
   size_t off = align256(size_t(ns_off));

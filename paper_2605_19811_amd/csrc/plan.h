@@ -130,8 +130,11 @@ Status validate_tensors(const TensorIn* x, int32_t n, std::string* err);
 // tensors' shapes, flags and 16-byte alignment only, never on their
 // addresses (those go into the per-call binding table). Its workspace size
 // does not depend on alignment either.
+// `small_tiles`: choose the launches' small tiles too (`fine`, `variant`); a
+// size query needs none of that.
 Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
-                  bool kappa_rms02, ChipShape chip, Plan* out, std::string* err);
+                  bool kappa_rms02, ChipShape chip, Plan* out, std::string* err,
+                  bool small_tiles = true);
 
 // Take the small-tile lists out of a plan (the launches then run gram, poly
 // and apply).

@@ -2,7 +2,10 @@
 // of each bf16 product of a list ("rows cols" pairs on the command line), and
 // checks the lists that replace the planner's tiles: every tile that holds
 // matrix data exactly once (the lower triangle for the symmetric products),
-// none past the padded buffers, each XCD segment a partition.
+// none past the padded buffers, each XCD segment a partition. Prints what the
+// choice costs, too.
+#include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <set>
@@ -62,6 +65,18 @@ int main(int argc, char** argv) {
       }
       bad += want != list.size();
     }
-  printf("bad %d\n", bad);
+  // least time of a plan with its small tiles over one without (a size query)
+  double us[2] = {1e9, 1e9};
+  for (int r = 0; r < 40; ++r) {
+    const auto t0 = std::chrono::steady_clock::now();
+    Plan q;
+    if (build_plan(x.data(), int32_t(x.size()), StepKind::kMuon, NsPrecision(), false, ChipShape(),
+                   &q, &err, r & 1) != Status::kOk)
+      return 1;
+    const auto t1 = std::chrono::steady_clock::now();
+    us[r & 1] = std::min(us[r & 1], std::chrono::duration<double, std::micro>(t1 - t0).count());
+    bad += q.ws_bytes != p.ws_bytes || (!(r & 1) && !q.fine[0][0].empty());
+  }
+  printf("bad %d cost %.2f\n", bad, us[1] / us[0]);
   return bad != 0;
 }
