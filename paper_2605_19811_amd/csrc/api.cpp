@@ -768,15 +768,24 @@ lm_status step_impl(float* const* params, const float* const* grads, float* cons
 // ---------------------------------------------------------------------------
 // No-allocation entry point
 // ---------------------------------------------------------------------------
-// Per device: the scratch array's device address and which list signature's
-// tables and which addresses it holds. Calls on one device share the array
-// and must not overlap.
+// Per device: the scratch array's device address, which list signature's
+// tables and which addresses it holds, and the plans of the last signatures on
+// the host. There are kNoallocPlans of those, the Lion and the Muon step of one
+// list: a loop with a period alternates between the two, and planning the Muon
+// step anew each time took longer (30-60 us for a matrix or a layer) than
+// uploading its tables. Calls on one device share the array and must not overlap.
+constexpr size_t kNoallocPlans = 2;
+struct NoallocPlan {
+  std::vector<uint8_t> key;
+  DevicePlan view;                        // the plan, its tables in scratch (not owned)
+  TableImage img;                         // what is uploaded, but for the binding
+  size_t ws_off = 0;                      // workspace offset in scratch
+};
 struct StaticScratch {
   int device = -1;
   uint8_t* ptr = nullptr;
-  std::vector<uint8_t> key;               // signature whose tables are resident
-  DevicePlan view;                        // the plan, its tables in scratch (not owned)
-  size_t ws_off = 0;                      // workspace offset in scratch
+  std::list<NoallocPlan> plans;           // most recent first
+  const NoallocPlan* resident = nullptr;  // the one whose tables are in scratch
 };
 std::vector<std::unique_ptr<StaticScratch>> g_static;
 
@@ -821,43 +830,56 @@ lm_status step_noalloc_impl(float* const* params, const float* const* grads,
   }
   std::vector<uint8_t> key = plan_key(device, x.data(), n, kind, prec, rms02);
   std::vector<lm::TensorPtrs> bind = binding_of(x.data(), n);
-  if (key != sc->key) {
-    // new signature: plan on the host, check the size limit, then upload
-    // the tables (and the binding) into the scratch array
-    Plan p;
+  auto known = sc->plans.begin();
+  while (known != sc->plans.end() && known->key != key) ++known;
+  if (known != sc->plans.end()) {
+    sc->plans.splice(sc->plans.begin(), sc->plans, known);
+  } else {
+    // new signature: plan on the host and check the size limit
+    std::list<NoallocPlan> fresh(1);
+    NoallocPlan& np = fresh.front();
+    Plan& p = np.view.plan;
     st = lm::build_plan(x.data(), n, kind, prec, rms02, chip_of(device), &p, &err);
     if (st != Status::kOk) return fail(to_c(st), err);
-    TableImage img;
-    pack_tables(p, bind, &img);
-    if (align256(img.bytes.size()) + p.ws_bytes > lm::kScratchBytes) {
+    pack_tables(p, bind, &np.img);
+    if (align256(np.img.bytes.size()) + p.ws_bytes > lm::kScratchBytes) {
       lm::drop_fine(&p);                   // the usual tiles are fewer
-      pack_tables(p, bind, &img);
+      pack_tables(p, bind, &np.img);
     }
-    const size_t ws_off = align256(img.bytes.size());
-    const size_t need = ws_off + p.ws_bytes;
+    np.ws_off = align256(np.img.bytes.size());
+    const size_t need = np.ws_off + p.ws_bytes;
     if (need > lm::kScratchBytes)
       return fail(LM_ERR_UNSUPPORTED,
                   "lionmuon_step_noalloc: this list needs " + std::to_string(need) +
                       " bytes of device scratch (plan tables and workspace); its static scratch "
                       "holds at most " + std::to_string(lm::kScratchBytes) +
                       " bytes (use lionmuon_step_ex for larger lists)");
-    sc->key.clear();                       // invalid until the upload is enqueued
-    e = lm::launch_upload(sc->ptr, img.bytes.data(), img.bytes.size(), stream);
-    if (e != hipSuccess) return hip_fail(e, "scratch: table upload");
-    sc->view.plan = std::move(p);
-    sc->view.bound.swap(bind);
-    point_tables(&sc->view, sc->ptr, img);
-    sc->ws_off = ws_off;
-    sc->key.swap(key);
-  } else if (!same_binding(sc->view.bound, bind)) {
-    e = lm::launch_upload(sc->view.d_bind, bind.data(), bind.size() * sizeof(lm::TensorPtrs),
-                          stream);
-    if (e != hipSuccess) return hip_fail(e, "scratch: address table upload");
-    sc->view.bound.swap(bind);
+    np.key.swap(key);
+    point_tables(&np.view, sc->ptr, np.img);
+    sc->plans.splice(sc->plans.begin(), fresh);
+    while (sc->plans.size() > kNoallocPlans) {
+      if (sc->resident == &sc->plans.back()) sc->resident = nullptr;
+      sc->plans.pop_back();
+    }
   }
-  void* ws = sc->view.plan.ws_bytes > 0 ? sc->ptr + sc->ws_off : nullptr;
+  NoallocPlan& np = sc->plans.front();
+  const size_t bind_bytes = bind.size() * sizeof(lm::TensorPtrs);
+  if (sc->resident != &np) {
+    // its tables, with this call's addresses, into the scratch array
+    std::memcpy(np.img.bytes.data() + np.img.o_bind, bind.data(), bind_bytes);
+    sc->resident = nullptr;                // until the upload is enqueued
+    e = lm::launch_upload(sc->ptr, np.img.bytes.data(), np.img.bytes.size(), stream);
+    if (e != hipSuccess) return hip_fail(e, "scratch: table upload");
+    np.view.bound.swap(bind);
+    sc->resident = &np;
+  } else if (!same_binding(np.view.bound, bind)) {
+    e = lm::launch_upload(np.view.d_bind, bind.data(), bind_bytes, stream);
+    if (e != hipSuccess) return hip_fail(e, "scratch: address table upload");
+    np.view.bound.swap(bind);
+  }
+  void* ws = np.view.plan.ws_bytes > 0 ? sc->ptr + np.ws_off : nullptr;
   g_prof_suppressed = true;
-  const lm_status s = enqueue(sc->view, step_consts(beta1, beta2, wd, cfg->lr_muon, cfg->lr_lion,
+  const lm_status s = enqueue(np.view, step_consts(beta1, beta2, wd, cfg->lr_muon, cfg->lr_lion,
                                                     cfg->ns_eps, cfg, t),
                               *cfg, ws, false, AdaptiveOut(), stream);
   g_prof_suppressed = false;
@@ -1123,6 +1145,10 @@ lm_status lionmuon_profiling_reset(void) {
 void lionmuon_release(void) {
   std::lock_guard<std::mutex> lock(g_mu);
   g_plans.clear();
+  for (auto& sc : g_static) {
+    sc->resident = nullptr;
+    sc->plans.clear();
+  }
   for (auto& reg : g_ring.inflight) {
     (void)hipEventSynchronize(reg.done);
     g_ring.pool.push_back(reg.done);

@@ -77,6 +77,22 @@ def test_noalloc_matches_step_ex_on_consecutive_calls():
     _check(small, [False, False], 84, 3, 3, "fp32")
 
 
+def test_noalloc_alternating_step_kinds():
+    """Muon and Lion steps of one list in turn (the tables of both plans are
+    uploaded again at each change), other buffers at each step, a third
+    signature in between, and after lionmuon_release."""
+    shapes, none = [(300, 700), (1, 90), (520, 128)], [False, False, False]
+    for t in range(4):
+        _check(shapes, none, [88, t], t, 2, "bf16")
+    _check([(64, 64)], [False], 89, 0, 1, "fp32")
+    for t in range(2):
+        _check(shapes, none, [90, t], t, 2, "bf16")
+    torch.cuda.synchronize()
+    lm.lionmuon_release()
+    for t in range(2):
+        _check(shapes, none, [91, t], t, 2, "bf16")
+
+
 def test_noalloc_matches_step_ex_on_random_lists():
     """Twelve seeded random lists in a row (3-8 tensors of random shape and
     orientation, some 1-D or Lion-only; both precisions; Muon and Lion
