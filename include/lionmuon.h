@@ -209,7 +209,9 @@ lm_status lionmuon_step_ex(float* const* params, const float* const* grads,
  * A list whose tables and workspace exceed the array fails with
  * LM_ERR_UNSUPPORTED before anything is enqueued (the message gives the
  * bytes needed): a Muon step over one 768x3072 bf16 matrix needs about
- * 12 MB, one 2048x4096 matrix about 50 MB.
+ * 12 MB, one 2048x4096 matrix about 50 MB. Within some KB of the limit, where
+ * the tables of the tiles that lionmuon_step_ex runs do not fit, the products
+ * run in larger ones: bf16 results are the same, fp32 ones differ by rounding.
  * All calls on one device share the array, which keeps the last call's
  * contents: calls on one device must not overlap (on different streams they
  * race); consecutive calls on one stream are ordered. No kernel reads scratch
@@ -278,10 +280,10 @@ typedef struct lm_plan_info {
   int64_t adamw_elements;   /* elements updated by AdamW                       */
   int64_t muon_elements;    /* elements on the Muon branch                     */
   int64_t gram_tiles, poly_tiles, apply_tiles; /* MFMA output tiles per NS step
-                               (a nearly empty last round of 256x256 apply tiles
-                               is counted as the smaller tiles it runs as; a
-                               list that leaves CUs idle at these tiles runs the
-                               same products in smaller ones)                   */
+                               in the usual tiles (a nearly empty last round of
+                               256x256 apply tiles counted as the smaller tiles it
+                               runs as). A launch that would leave CUs idle runs
+                               the same product in more, smaller ones           */
   double ns_flops;          /* algorithmic NS flops, symmetric products counted
                                once: K * sum s(s+1)l + s^2(s+1) + 2 s^2 l       */
   double ns_flops_dense;    /* dense convention K * sum 4 s^2 l + 2 s^3        */
@@ -315,7 +317,7 @@ lm_status lionmuon_profiling_enable(int32_t enable);
 lm_status lionmuon_profiling_read(lm_phase_times* out);
 lm_status lionmuon_profiling_reset(void);
 
-/* Free the library-owned workspace and cached plans (device memory). Must not
+/* Free the library-owned workspace and cached plans. Must not
  * be called while work enqueued by this library is still running. */
 void lionmuon_release(void);
 

@@ -1,5 +1,6 @@
 // Host-only driver for tests/test_small_tiles.py: prints the small-tile variant
-// of each bf16 product of a list ("rows cols" pairs on the command line), and
+// of each product of a list ("bf16" or "fp32", then "rows cols" pairs, on the
+// command line), and
 // checks the lists that replace the planner's tiles: every tile that holds
 // matrix data exactly once (the lower triangle for the symmetric products),
 // none past the padded buffers, each XCD segment a partition. Prints what the
@@ -18,7 +19,9 @@ using namespace lm;
 
 int main(int argc, char** argv) {
   std::vector<TensorIn> x;
-  for (int i = 1; i + 1 < argc; i += 2) {
+  NsPrecision prec;
+  prec.all_fp32 = argc > 1 && std::string(argv[1]) == "fp32";
+  for (int i = 2; i + 1 < argc; i += 2) {
     TensorIn t{};
     const uintptr_t base = 0x100000000ull + uintptr_t(i) * 0x1000000000ull;
     t.w = reinterpret_cast<float*>(base);
@@ -30,7 +33,7 @@ int main(int argc, char** argv) {
   }
   Plan p;
   std::string err;
-  if (build_plan(x.data(), int32_t(x.size()), StepKind::kMuon, NsPrecision(), false, ChipShape(), &p,
+  if (build_plan(x.data(), int32_t(x.size()), StepKind::kMuon, prec, false, ChipShape(), &p,
                  &err) != Status::kOk)
     return 1;
   int bad = 0;
@@ -38,7 +41,7 @@ int main(int argc, char** argv) {
     for (int st = 0; st < 3; ++st) {
       const GemmVariant& v = p.variant[pr][st];
       const std::vector<GemmTask>& list = p.fine[pr][st];
-      if (pr == 0) printf("%d/%d ", v.tile, v.bufs);
+      if (pr == (prec.all_fp32 ? 1 : 0)) printf("%d/%d ", v.tile, v.bufs);
       if (v.tile == 0) {
         bad += !list.empty();
         continue;
@@ -70,7 +73,7 @@ int main(int argc, char** argv) {
   for (int r = 0; r < 40; ++r) {
     const auto t0 = std::chrono::steady_clock::now();
     Plan q;
-    if (build_plan(x.data(), int32_t(x.size()), StepKind::kMuon, NsPrecision(), false, ChipShape(),
+    if (build_plan(x.data(), int32_t(x.size()), StepKind::kMuon, prec, false, ChipShape(),
                    &q, &err, r & 1) != Status::kOk)
       return 1;
     const auto t1 = std::chrono::steady_clock::now();

@@ -26,6 +26,10 @@ LISTS = {
     "apply-128": ([(768, 2304), (768, 768), (768, 3072), (3070, 766)], "64/4 64/4 128/2"),
     "poly-two-stage": ([(2000, 2000)], "64/2 64/2 64/2"),
     "gram-small-only": ([(768, 2304), (768, 768), (768, 3072), (3072, 768)] * 3, "64/4 0/2 0/2"),
+    # small tiles for one product and the usual ones for the next, which then read
+    # padding that the small ones did not write
+    "ragged-gram-only": ([(765, 2300), (765, 765), (765, 3070), (3070, 765)] * 3, "64/4 0/2 0/2"),
+    "ragged-apply-usual": ([(901, 2703), (901, 901), (901, 3604), (3604, 901)], "64/4 64/4 0/2"),
 }
 
 
@@ -38,8 +42,9 @@ def planner(tmp_path_factory):
                     os.path.join(HERE, "planner_small_tiles_driver.cpp"),
                     os.path.join(CSRC, "plan.cpp"), "-o", exe], check=True)
 
-    def run(shapes):
-        out = subprocess.run([exe, *(str(v) for s in shapes for v in s)], capture_output=True, text=True)
+    def run(shapes, prec="bf16"):
+        args = [str(v) for s in shapes for v in s]
+        out = subprocess.run([exe, prec, *args], capture_output=True, text=True)
         assert out.returncode == 0, out.stdout
         return out.stdout
     return run
@@ -48,6 +53,10 @@ def planner(tmp_path_factory):
 def test_planner_small_tile_lists(planner):
     for name, (shapes, variants) in LISTS.items():
         assert planner(shapes).split("bad")[0].strip() == variants, name
+    # (the list of test_noalloc_where_only_the_usual_tiles_fit)
+    assert planner([(1792, 7424), (256, 512)]).startswith("64/4 64/4 0/2")
+    for name, (shapes, variants) in F32_LISTS.items():
+        assert planner(shapes, "fp32").split("bad")[0].strip() == variants, name
 
 
 # A plan is built anew wherever list signatures alternate beyond those that are
@@ -106,13 +115,15 @@ def test_bf16_result_does_not_depend_on_the_list(shape):
         assert torch.equal(lm.lionmuon_ns(x[i].contiguous(), cfg), many[i])
 
 
-# fp32 products: K loops of 1 to 9 stages of 64 on 64-tiles (a round is 8), tile edges,
-# and (the pair of 1000 x 1500) 128-tiles with an odd number of stages of 32
+# fp32 products: K loops of 1 to 9 and 18 stages of 64 on 64-tiles (a round is 8),
+# tile edges, the apply alone on 128-tiles, and all three products on 128-tiles
+# with 47 and 63 stages of 32 (odd, and no multiple of a round's four)
 F32_LISTS = {
-    "one-stage": [(2, 3), (33, 64), (64, 40)],
-    "edges": [(65, 129), (129, 193), (257, 191), (63, 449)],
-    "rounds": [(512, 513), (577, 513), (100, 1089)],
-    "tile-128": [(1000, 1510), (1510, 1000), (980, 1510)],
+    "one-stage": ([(2, 3), (33, 64), (64, 40)], "64/2 64/2 64/2"),
+    "edges": ([(65, 129), (129, 193), (257, 191), (63, 449)], "64/2 64/2 64/2"),
+    "rounds": ([(512, 513), (577, 513), (100, 1089)], "64/2 64/2 64/2"),
+    "apply-128": ([(1000, 3000), (1000, 3000)], "64/2 64/2 128/2"),
+    "tile-128": ([(1500, 2000), (2000, 1500)], "128/2 128/2 128/2"),
 }
 
 
@@ -123,7 +134,7 @@ def test_split_fp32_products_match_oracle(name):
 
     from paper_2605_19811_amd import lionmuon as lm
     from parity import check_muon
-    shapes = F32_LISTS[name]
+    shapes = F32_LISTS[name][0]
     rng = np.random.default_rng(len(shapes) + shapes[0][0])
     W0, M0, G = ([(rng.standard_normal(s) * std).astype(np.float32) for s in shapes]
                  for std in (0.02, 1e-2, 1e-2))

@@ -121,6 +121,46 @@ def test_noalloc_matches_step_ex_on_random_lists():
     assert done >= 10
 
 
+def test_noalloc_where_only_the_usual_tiles_fit():
+    """Two bf16 matrices whose workspace leaves 0.2 MiB of the scratch for the
+    tables, and as many one-element tensors as it accepts: there the tables of
+    the small tiles that step_ex runs (64-tiles for Gram and polynomial) do not
+    fit, and the call falls back to the usual tiles. bf16 results are the same."""
+    mats = [(1792, 7424), (256, 512)]
+    need = lm.lionmuon_workspace_bytes([(*s, False) for s in mats])
+    room = lm.NOALLOC_SCRATCH_BYTES - need
+    assert 0 < room < 1 << 18
+    most = room // 64                          # (its entries in the tables take 64 bytes)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(92)
+    cfg = lm.config(lr_muon=0.02, lr_lion=1e-3)
+    x = [[torch.randn(s, generator=gen, device=DEV) * 1e-2 for s in mats] for _ in range(3)]
+    small = [torch.randn((most, 1), generator=gen, device=DEV) * 1e-2 for _ in range(3)]
+
+    def step(call, n):
+        W, G, M = ([v.clone() for v in big] + list(flat.clone()[:n])
+                   for big, flat in zip(x, small))
+        call(W, G, M, 0, 1, 0.9, 0.99, 0.1, cfg)
+        torch.cuda.synchronize()
+        return W, M
+
+    def fits(n):
+        try:
+            return step(lm.lionmuon_step_noalloc, n)
+        except lm.LionMuonError as e:
+            assert e.status == lm.LM_ERR_UNSUPPORTED
+            return None
+    low, high = 0, most
+    assert fits(low) and not fits(high)
+    while high - low > 1:
+        mid = (low + high) // 2
+        low, high = (mid, high) if fits(mid) else (low, mid)
+    # with the small tiles' lists alone (8 bytes a tile) it would not have fitted
+    assert 64 * low + 2 * 8 * (28 * 29 // 2 + 4 * 5 // 2) > room
+    (W, M), (We, Me) = fits(low), step(lm.lionmuon_step_ex, low)
+    assert all(torch.equal(a, b) for a, b in zip(W + M, We + Me))
+
+
 def test_noalloc_rejects_a_list_beyond_its_scratch():
     """A Muon step whose workspace exceeds the scratch is refused before
     anything is enqueued; a Lion step on the same list (no workspace) runs."""
