@@ -31,7 +31,9 @@ import workloads  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0            # MI355X HBM3E
 BF16_PEAK_TFLOPS = 2516.6         # dense MFMA: 256 CU x 2.4 GHz x 4096 flop/clk
-FP32_MFMA_PEAK_TFLOPS = 157.3
+# fp32 products: each is six bf16 MFMA terms of values split into three bf16 parts
+FP32_TERMS = 6
+FP32_SPLIT_PEAK_TFLOPS = round(BF16_PEAK_TFLOPS / FP32_TERMS, 1)
 # the kernels, the planner that sets their tiles and grids, and the constants
 # both share: traffic per launch depends on all three
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2605_19811_amd", "csrc", f)
@@ -158,13 +160,13 @@ def sq_summary(wl_name, sq_csvs, command):
     """MFMA issue and utilisation of each Newton-Schulz phase from rocprofv3
     counter passes (one CSV per pass; per-dispatch durations from the CSV's
     timestamps), against the phase's algorithmic flops: issued flops = 512
-    SQ_INSTS_VALU_MFMA_MOPS_BF16 (F32 for fp32 products)."""
+    SQ_INSTS_VALU_MFMA_MOPS_BF16 (fp32 products: six bf16 terms each)."""
     import collections
     import csv
     wl = workloads.get(wl_name.replace("-adaptive", ""))
     algo = ns_flops_per_launch(wl)
     fp32 = wl.ns_precision == "fp32"
-    peak_tflops = FP32_MFMA_PEAK_TFLOPS if fp32 else BF16_PEAK_TFLOPS
+    peak_tflops = FP32_SPLIT_PEAK_TFLOPS if fp32 else BF16_PEAK_TFLOPS
     # per phase: counter sums, per-dispatch durations and dispatch counts
     cnt = collections.defaultdict(lambda: collections.defaultdict(float))
     dur = collections.defaultdict(dict)          # phase -> {(pass, dispatch): ns}
@@ -188,9 +190,10 @@ def sq_summary(wl_name, sq_csvs, command):
              "- `algorithmic frac`: the phase's symmetric flop count (Gram s(s+1)l, polynomial "
              "s^2(s+1), apply 2 s^2 l per matrix) over the launch duration, against the dense "
              "MFMA peak of the path's type: bf16 2516.6 TFLOP/s (256 CUs x 2.4 GHz x 4096 "
-             "flop/clk), fp32 157.3 TFLOP/s" + (" (this workload: fp32)." if fp32 else "."),
-             "- `issued frac`: 512 x SQ_INSTS_VALU_MFMA_MOPS_BF16 (+_F32) flops over the same "
-             "duration and peak: the MFMA work the kernels actually execute.",
+             "flop/clk), fp32 a sixth of it (419.4; six bf16 MFMA terms a product)"
+             + (" (this workload: fp32)." if fp32 else "."),
+             "- `issued frac`: 512 x SQ_INSTS_VALU_MFMA_MOPS_BF16 flops (fp32: a sixth of them) "
+             "over the same duration and peak: the MFMA work the kernels actually execute.",
              "- `issued / algorithmic`: MFMA work spent per useful flop. Above 1 where a "
              "symmetric product computes its diagonal tiles in full and where padding to the "
              "tile edge adds rows.",
@@ -212,8 +215,9 @@ def sq_summary(wl_name, sq_csvs, command):
         c = cnt[ph]
         launches = len(n256[ph]) or len(nall[ph])
         t_ns = sum(dur[ph].values()) / launches
-        issued = 512.0 * (c.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0) +
-                          c.get("SQ_INSTS_VALU_MFMA_MOPS_F32", 0.0)) / launches
+        issued = 512.0 * c.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0) / launches
+        if fp32:
+            issued /= FP32_TERMS
         peak = peak_tflops * 1e12 * t_ns * 1e-9
         cycles = c.get("GRBM_GUI_ACTIVE", 0.0) / XCDS / launches
         util = c.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / launches / (cycles * SIMDS) if cycles else 0.0
@@ -528,7 +532,7 @@ class Bench:
             n_muon_steps = sum(1 for k in range(steps) if P >= 1 and (t_start + k) % P == 0)
         n_lion_steps = steps - n_muon_steps
         flops = ns_flops_per_launch(wl)
-        peak_mfma = BF16_PEAK_TFLOPS if wl.ns_precision == "bf16" else FP32_MFMA_PEAK_TFLOPS
+        peak_mfma = BF16_PEAK_TFLOPS if wl.ns_precision == "bf16" else FP32_SPLIT_PEAK_TFLOPS
         ph = {}
         for name, v in phases.items():
             if v["launches"] == 0:
@@ -613,7 +617,8 @@ def workload_config(wl, info):
             "ns_steps": 5, "gradients": wl.grad_dist,
             "state": "fp32 W, M, G; " + ("bf16 MFMA Newton-Schulz with fp32 accumulation"
                                          if wl.ns_precision == "bf16"
-                                         else "fp32 MFMA Newton-Schulz")}
+                                         else "fp32 Newton-Schulz products as six bf16 MFMA terms "
+                                              "of exactly split values")}
 
 
 def main():

@@ -264,9 +264,9 @@ int64_t launch_bound(const std::vector<Run>& runs, int slots, StageCost c, ChipS
 void pick_fine(Plan* p, int pr, int st) {
   const std::vector<GemmTask>& macro = st == 0 ? p->gram[pr] : (st == 1 ? p->poly[pr] : p->apply[pr]);
   const size_t cus = size_t(p->chip.cus);
-  // (From eight rounds of the usual tiles on the chip is full, and no small tile
-  // was ever estimated or measured faster in bf16. fp32 lists that long keep
-  // their 128-tiles: the constants were fitted to shorter ones.)
+  // (Lists of eight rounds of the usual tiles and more keep them: there the chip
+  // is full, and 24 layers of 1280 gain nothing. Thousands of matrices smaller
+  // than a tile would; the constants were not fitted to such lists.)
   if (macro.empty() || macro.size() >= 8 * cus || p->chip.cus < p->chip.xcds) return;
   struct Choice {
     GemmVariant v;
@@ -591,7 +591,8 @@ Status build_plan(const TensorIn* x, int32_t n, StepKind kind, NsPrecision prec,
   // bf16: apply on 256-tiles; Gram and polynomial (s x s outputs, lower
   // triangle) each on whichever of 256- and 128-tiles the launch estimate
   // below favours. fp32: 128-tiles, or 64-tiles for a product whose
-  // 128-tiles would not give every CU one.
+  // 128-tiles would not give every CU one (lists past pick_fine's limit, or
+  // where its tables do not fit; every other fp32 list takes the tiles it picks).
   if (p->mats.size() > 0) {
     p->tile[0][0] = pick_sym_tile(p->mats, true, chip);
     p->tile[0][1] = pick_sym_tile(p->mats, false, chip);
